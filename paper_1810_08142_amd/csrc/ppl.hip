@@ -23,7 +23,8 @@
 // amplitudes (cd side) or are skipped when unpacking (ab side).
 //
 // Pipeline per call (all on the caller's stream):
-//   1. relayout   Bc[c][Q][a] = B_vv[Q][a][c]           (MFMA-operand layout, zero padded)
+//   1. relayout   Bc[c][a / 16][Q][a % 16] = B_vv[Q][a][c] (MFMA-operand layout, zero padded:
+//                 the 16 columns of one block are one contiguous run over Q)
 //   2. pack       T+[cd slot][i<=j], T-[cd slot][i<j]     (sigma and the 1/2 folded in)
 //   3. per slab of ab block pairs:
 //      build      W+-[cd slot][ab slot] = (ac|bd) +- (ad|bc)  (MFMA over Q, B staged in LDS)
@@ -70,6 +71,20 @@ struct Mfma<float> {
   __device__ static acc_t zero() { return acc_t{0.f, 0.f, 0.f, 0.f}; }
 };
 
+// One 16-byte global load per lane straight into LDS, lane l of the wave to
+// dst + 16 l bytes (dst uniform over the wave).  Counted by vmcnt; nothing else waits
+// for it, so a ring of LDS stages pairs it with stage_barrier.
+__device__ __forceinline__ void load_lds16(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+// Workgroup barrier once this wave's LDS accesses are done and at most N of its newest
+// vector memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // ---------------------------------------------------------------- 1. relayout
 // B[q][a][c] lives at B + q*qs + a*rs + c.  grid (naux_p, vp/16, vp/16), block 256
 template <class T>
@@ -81,7 +96,7 @@ __device__ __forceinline__ void relayout_body(const double* __restrict__ B, long
   const int a = a0 + ty, c = c0 + tx;
   tile[ty][tx] = (a < v && c < v && q < naux) ? B[q * qs + a * rs + c] : 0.0;
   __syncthreads();
-  Bc[(static_cast<size_t>(c0 + ty) * naux_p + q) * vp + a0 + tx] = static_cast<T>(tile[tx][ty]);
+  Bc[((static_cast<size_t>(c0 + ty) * gridDim.y + blockIdx.y) * naux_p + q) * TB + tx] = static_cast<T>(tile[tx][ty]);
 }
 __global__ __launch_bounds__(256) void relayout_b_f64(const double* __restrict__ B, long qs, long rs, int v,
                                                       int naux, int vp, int naux_p, double* __restrict__ Bc) {
@@ -144,30 +159,54 @@ __global__ __launch_bounds__(256) void pack_tau_f32(const double* __restrict__ t
 }
 
 // ---------------------------------------------------------------- 3a. build
-// One workgroup: ab block pair (Ab, Bb) x one quarter (8 c by 8 d) of cd block pair
-// (Cb, Db).  Eight waves; wave w owns c in {2*(w>>1), +1} and d in {4*(w&1) .. +3}
-// of the quarter and accumulates (ac|bd) and (ad|bc) as 16x16 (a, b) MFMA tiles.
-// LDS holds, per KC-wide Q chunk, Bc for the 16 c/d rows x (16 a + 16 b) columns.
+// One workgroup: ab block pair (Ab, Bb) x a part of cd block pair (Cb, Db): 2 NWC
+// consecutive c by 8 d.  2 NWC waves; wave w owns c in {2*(w>>1), +1} and
+// d in {4*(w&1) .. +3} of the part and accumulates (ac|bd) and (ad|bc) as 16x16 (a, b)
+// MFMA tiles.  A stage of LDS holds, for SK = 8 auxiliary functions, Bc for the
+// 2 NWC + 8 c/d rows x (16 a + 16 b) columns.
 // The launch covers cd block pairs pcd0 .. nbp-1 (rows of the others are not written).
-// grid ((nbp - pcd0)*4, slab_pairs), block 512
+// grid ((nbp - pcd0)*16/NWC, slab_pairs), block 128*NWC
 // D: the workgroups of diagonal ab block pairs (Ab == Bb), blockIdx.y counting them
 // from block Ab = diag_y0; otherwise blockIdx.y is the slab's pair and diagonal pairs
 // exit at once.  In a diagonal pair a and b run over the same block, so the (ad|bc)
 // tile is the transpose of the (ac|bd) tile: only the latter is built, and the
 // epilogue reads it back transposed through LDS.
+//
+// Bound by the FP64 (FP32) matrix pipe.  The factors go straight from memory to a ring of
+// three LDS stages, loaded two stages ahead; one barrier per stage, taken before the
+// stage's last step, makes the next stage visible and frees the previous one, and the
+// operands of each step are read one step ahead.  The workgroup of NWC = 2 (four waves,
+// 72 KB) shares its CU with a second one, whose products fill the pipe while this one
+// waits, starts or stores W.  The loop has no branches: past the last stage it loads that
+// stage again into idle slots.  A launch of 68
+// block pairs at v=256 naux=768 takes 23.4 ms in FP64 (25.9 ms with eight waves, registers
+// between memory and LDS, and [c][Q][a] factors, whose 128-byte pieces lay a whole number
+// of L2 channel rounds apart and queued on one channel); 2.18 ms in FP32 at v=150 naux=421
+// (2.29 ms).
 template <class T, bool D>
+struct BuildFrag {
+  T a_c[2], b_c[D ? 1 : 2], a_d[D ? 1 : 4], b_d[4];
+};
+template <class T, bool D, int NWC>
 __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p, int vp, long slab0, long slab_M,
                                            int want_minus, int diag_y0, long pcd0, T* __restrict__ Wp,
                                            T* __restrict__ Wm) {
   typedef Mfma<T> MF;
-  typedef typename MF::vec_t vec_t;
+  constexpr int NT = 128 * NWC;                // threads
+  constexpr int NC = 2 * NWC, NX = NC + 8;     // c rows, all rows
+  constexpr int PARTS = 16 / NWC;              // workgroups per cd block pair
   constexpr int VEC = 16 / sizeof(T);          // elements per 16-byte load
-  constexpr int EV = 32 / VEC;                 // loads per (x, k) row of 32 e
-  constexpr int NV = 16 * KC * 32 / (512 * VEC);  // loads per thread per chunk
-  __shared__ T lds[2][16][KC][32];  // [buf][x: 8 c then 8 d][k][e: 16 a then 16 b]
-  static_assert(2 * 16 * KC * 32 >= 8 * 8 * 256, "the staging buffer holds the transposed tiles");
-  const int quarter = blockIdx.x & 3;
-  const long pcd = pcd0 + (blockIdx.x >> 2);
+  constexpr int SK = 8;                        // auxiliary functions per stage
+  constexpr int EV = 16 * SK / VEC;            // loads per (row, a or b block) of a stage: one wave's
+  constexpr int LBUF = NX * 2 * SK * TB;       // elements of one stage
+  constexpr int NV = LBUF / (NT * VEC);        // loads per thread per stage
+  constexpr int NS = SK / 4;                   // MFMA steps per stage
+  static_assert(NS % 2 == 0 && KC % SK == 0, "operand registers alternate over whole stages");
+  static_assert(NV * NT * VEC == LBUF, "whole loads");
+  __shared__ T lds[3 * LBUF];  // [slot][x: NC c then 8 d][a or b][k][16 e]
+  static_assert(3 * LBUF >= 2 * NWC * 4 * 256, "the ring holds half of the transposed tiles");
+  const int part = blockIdx.x % PARTS;
+  const long pcd = pcd0 + blockIdx.x / PARTS;
   int Cb, Db, Ab, Bb;
   tri_decode(pcd, Cb, Db);
   long pab_loc;
@@ -179,34 +218,28 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
     tri_decode(slab0 + pab_loc, Ab, Bb);
     if (Ab == Bb) return;  // built by the diagonal launch (uniform over the workgroup)
   }
-  const int c_base = Cb * TB + (quarter >> 1) * 8;
-  const int d_base = Db * TB + (quarter & 1) * 8;
+  const int c_off = (part >> 1) * NC, d_off = (part & 1) * 8;
+  const int c_base = Cb * TB + c_off, d_base = Db * TB + d_off;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
 
-  // global -> register -> LDS staging: NV 16-byte loads per thread per chunk.
-  // Offsets are computed once; the chunk loop only adds the Q stride.
-  size_t goff[NV];
-  int loff[NV];
+  // staging: NV 16-byte loads per thread per stage, addresses computed once.
+  // Run p2 of a stage: row x, then a or b block, then 16 SK consecutive elements.
+  const T* gp[NV];
 #pragma unroll
   for (int r = 0; r < NV; ++r) {
-    const int p2 = t + 512 * r;
-    const int x = p2 / (KC * EV), k = (p2 / EV) % KC, e = (p2 % EV) * VEC;
-    const int cg = x < 8 ? c_base + x : d_base + (x - 8);
-    const int ag = e < 16 ? Ab * TB + e : Bb * TB + (e - 16);
-    goff[r] = (static_cast<size_t>(cg) * naux_p + k) * vp + ag;
-    loff[r] = (x * KC + k) * 32 + e;
+    const int p2 = t + NT * r;
+    const int x = p2 / (2 * EV), h = p2 / EV % 2, ke = p2 % EV * VEC;
+    const int cg = x < NC ? c_base + x : d_base + (x - NC);
+    gp[r] = Bc + (static_cast<size_t>(cg) * (vp / TB) + (h ? Bb : Ab)) * naux_p * TB + ke;
   }
-  const size_t qstride = static_cast<size_t>(vp) * KC;  // advance one chunk of Q
-  T* lds0 = &lds[0][0][0][0];
-  constexpr int LBUF = 16 * KC * 32;
-
-  const int xc0 = (w >> 1) * 2, xd0 = 8 + (w & 1) * 4;
+  const int wv = __builtin_amdgcn_readfirstlane(w);
+  const int xc0 = (w >> 1) * 2, xd0 = NC + (w & 1) * 4;
   const int m = lane & 15, kq = lane >> 4;
-  const int nchunks = naux_p / KC;
-  // In a diagonal cd block pair the quarter with c in the upper and d in the lower
-  // half holds only c > d slots, whose packed amplitudes are zero: its W entries are
-  // written as zeros without the build (uniform over the workgroup).
-  const bool skip = Cb == Db && quarter == 2;
+  const int nst = naux_p / SK;
+  // In a diagonal cd block pair a part with all c above all d holds only slots whose
+  // packed amplitudes are zero: its W entries are written as zeros without the build
+  // (uniform over the workgroup).
+  const bool skip = Cb == Db && c_off > d_off + 7;
   const size_t col0 = static_cast<size_t>(pab_loc) * 256;
 
   {
@@ -221,87 +254,83 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc2[i][j] = MF::zero();
     if (!skip) {
-      vec_t stage[NV];
+      auto gload = [&](int st, int slot) {
+        const size_t at = static_cast<size_t>(st) * (SK * TB);
 #pragma unroll
-      for (int r = 0; r < NV; ++r) stage[r] = *reinterpret_cast<const vec_t*>(Bc + goff[r]);
+        for (int r = 0; r < NV; ++r) load_lds16(gp[r] + at, lds + slot * LBUF + (wv * 64 + NT * r) * VEC);
+      };
+      const int fc = (xc0 * 2 * SK + kq) * TB + m, fd = (xd0 * 2 * SK + kq) * TB + m;
+      BuildFrag<T, D> f[2];
+      auto fread = [&](BuildFrag<T, D>& q, int slot, int s) {  // step s of the stage in `slot`
+        const T* base = lds + slot * LBUF + s * 4 * TB;
 #pragma unroll
-      for (int r = 0; r < NV; ++r) *reinterpret_cast<vec_t*>(lds0 + loff[r]) = stage[r];
-      __syncthreads();
-      for (int ch = 0; ch < nchunks; ++ch) {
-        const int buf = ch & 1;
-        const bool more = ch + 1 < nchunks;
-        if (more) {
-          const size_t qo = static_cast<size_t>(ch + 1) * qstride;
-#pragma unroll
-          for (int r = 0; r < NV; ++r) stage[r] = *reinterpret_cast<const vec_t*>(Bc + goff[r] + qo);
+        for (int i = 0; i < 2; ++i) {
+          q.a_c[i] = base[fc + 2 * i * SK * TB];
+          if constexpr (!D) q.b_c[i] = base[fc + (2 * i + 1) * SK * TB];
         }
 #pragma unroll
-        for (int s = 0; s < KC / 4; ++s) {
-          const int kk = 4 * s + kq;
-          if constexpr (D) {
-            T a_c[2], b_d[4];
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (!D) q.a_d[j] = base[fd + 2 * j * SK * TB];
+          q.b_d[j] = base[fd + (2 * j + 1) * SK * TB];
+        }
+      };
+      auto mma = [&](const BuildFrag<T, D>& q) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a_c[i] = lds[buf][xc0 + i][kk][m];
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b_d[j] = lds[buf][xd0 + j][kk][16 + m];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) acc1[i][j] = MF::mma(a_c[i], b_d[j], acc1[i][j]);  // (ac|bd)
-          } else {
-            T a_c[2], b_c[2], a_d[4], b_d[4];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-              a_c[i] = lds[buf][xc0 + i][kk][m];
-              b_c[i] = lds[buf][xc0 + i][kk][16 + m];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              a_d[j] = lds[buf][xd0 + j][kk][m];
-              b_d[j] = lds[buf][xd0 + j][kk][16 + m];
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                acc1[i][j] = MF::mma(a_c[i], b_d[j], acc1[i][j]);      // (ac|bd)
-                acc2[i % NA2][j] = MF::mma(a_d[j], b_c[i], acc2[i % NA2][j]);  // (ad|bc)
-              }
+          for (int j = 0; j < 4; ++j) {
+            acc1[i][j] = MF::mma(q.a_c[i], q.b_d[j], acc1[i][j]);                    // (ac|bd)
+            if constexpr (!D) acc2[i][j] = MF::mma(q.a_d[j], q.b_c[i], acc2[i][j]);  // (ad|bc)
           }
-        }
-        if (more) {
-          T* dst = lds0 + (buf ^ 1) * LBUF;
+      };
+      const int last = nst - 1;
+      gload(0, 0);
+      gload(min(1, last), 1);
+      stage_barrier<NV>();
+      fread(f[0], 0, 0);
+      int s0 = 0, s1 = 1, s2 = 2;  // slots of stages st, st + 1, st + 2
+      for (int st = 0; st < nst; ++st) {
+        gload(min(st + 2, last), s2);
 #pragma unroll
-          for (int r = 0; r < NV; ++r) *reinterpret_cast<vec_t*>(dst + loff[r]) = stage[r];
+        for (int s = 0; s < NS; ++s) {
+          if (s + 1 < NS) {
+            fread(f[(s + 1) & 1], s0, s + 1);
+          } else {
+            stage_barrier<NV>();  // all but the loads of this pass: stage st + 1 is whole
+            fread(f[(s + 1) & 1], s1, 0);
+          }
+          mma(f[s & 1]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
+        const int sf = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = sf;
       }
+      stage_barrier<0>();  // no load is left to land in the ring
     }  // !skip
 
-    // each wave's own 8 x 256 elements of the (now idle) staging buffer hold its
-    // (ac|bd) tiles, element (a, b) of a tile at a*16 + (b ^ a)
-    T* tw = lds0 + w * (8 * 256);
-    if constexpr (D) {
+    // epilogue: W+-[slot][ab slot]; element r of a lane is row a_in = drow(r, lane),
+    // column b_in = lane & 15 of the (a, b) tile.  D: each wave's own 4 x 256 elements of
+    // the (now idle) ring hold the (ac|bd) tiles of one c, element (a, b) of a tile at
+    // a*16 + (b ^ a), read back transposed.
+    T* tw = lds + w * (4 * 256);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (D) {
+        if (i) __syncthreads();
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int a_in = MF::drow(r, lane), b_in = lane & 15;
-            tw[(i * 4 + j) * 256 + a_in * 16 + (b_in ^ a_in)] = acc1[i][j][r];
+            tw[j * 256 + a_in * 16 + (b_in ^ a_in)] = acc1[i][j][r];
           }
-      __syncthreads();
-    }
-
-    // epilogue: W+-[slot][ab slot]; element r of a lane is row a_in = drow(r, lane),
-    // column b_in = lane & 15 of the (a, b) tile.
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
+        __syncthreads();
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int c_in = (quarter >> 1) * 8 + xc0 + i;
-        const int d_in = (quarter & 1) * 8 + (xd0 - 8) + j;
+        const int c_in = c_off + xc0 + i, d_in = d_off + (xd0 - NC) + j;
         const size_t row = (static_cast<size_t>(pcd) * 256 + c_in * 16 + d_in) * slab_M + col0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -309,31 +338,35 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
           const T v1 = acc1[i][j][r];
           T v2;
           if constexpr (D)
-            v2 = tw[(i * 4 + j) * 256 + b_in * 16 + (a_in ^ b_in)];  // (ac|bd)[b][a]
+            v2 = tw[j * 256 + b_in * 16 + (a_in ^ b_in)];  // (ac|bd)[b][a]
           else
             v2 = acc2[i][j][r];
           Wp[row + a_in * 16 + b_in] = v1 + v2;
           if (want_minus) Wm[row + a_in * 16 + b_in] = v1 - v2;
         }
       }
+    }
   }
 }
-__global__ __launch_bounds__(512) void build_w_f64(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
+constexpr int BNW = 2;  // c pairs per build workgroup
+#define BUILD_ATTR(w) __launch_bounds__(128 * BNW) __attribute__((amdgpu_waves_per_eu(w, w)))
+__global__ BUILD_ATTR(2) void build_w_f64(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
     long slab_M, int want_minus, int diag_y0, long pcd0, double* __restrict__ Wp, double* __restrict__ Wm) {
-  build_body<double, false>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+  build_body<double, false, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
-__global__ __launch_bounds__(512) void build_w_f64_diag(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
+__global__ BUILD_ATTR(2) void build_w_f64_diag(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
     long slab_M, int want_minus, int diag_y0, long pcd0, double* __restrict__ Wp, double* __restrict__ Wm) {
-  build_body<double, true>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+  build_body<double, true, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
-__global__ __launch_bounds__(512) void build_w_f32(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
+__global__ BUILD_ATTR(4) void build_w_f32(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
     long slab_M, int want_minus, int diag_y0, long pcd0, float* __restrict__ Wp, float* __restrict__ Wm) {
-  build_body<float, false>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+  build_body<float, false, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
-__global__ __launch_bounds__(512) void build_w_f32_diag(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
+__global__ BUILD_ATTR(4) void build_w_f32_diag(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
     long slab_M, int want_minus, int diag_y0, long pcd0, float* __restrict__ Wp, float* __restrict__ Wm) {
-  build_body<float, true>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+  build_body<float, true, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
+#undef BUILD_ATTR
 
 // ---------------------------------------------------------------- 3b. contract
 // C[m][n] = sum_k W[k][m] T[k][n];  tile CRM (m) x 16*NTW (n); 4 waves, wave w owns
@@ -448,7 +481,7 @@ __device__ __forceinline__ void contract_body(const T* __restrict__ W, const T* 
       }
 }
 template <int NTW>
-__global__ __launch_bounds__(256) void contract_f64(const double* __restrict__ W, const double* __restrict__ Tt,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_f64(const double* __restrict__ W, const double* __restrict__ Tt,
                                                     long K, long M, int ncol, double* __restrict__ C, long kz,
                                                     long zs) {
   contract_body<double, NTW>(W, Tt, K, M, ncol, C, kz, zs);
@@ -570,13 +603,13 @@ __device__ __forceinline__ void contract_rows_body(const T* __restrict__ W, long
       }
 }
 template <int NTW>
-__global__ __launch_bounds__(256) void contract_rows_f64(const double* __restrict__ W, long ldw,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_rows_f64(const double* __restrict__ W, long ldw,
                                                          const double* __restrict__ Tt, long M, int ncol,
                                                          double* __restrict__ C, int accum) {
   contract_rows_body<double, NTW>(W, ldw, Tt, M, ncol, C, accum);
 }
 template <int NTW>
-__global__ __launch_bounds__(256) void contract_rows_f32(const float* __restrict__ W, long ldw,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_rows_f32(const float* __restrict__ W, long ldw,
                                                          const float* __restrict__ Tt, long M, int ncol,
                                                          float* __restrict__ C, int accum) {
   contract_rows_body<float, NTW>(W, ldw, Tt, M, ncol, C, accum);
@@ -720,48 +753,28 @@ struct Plan {
   int po, pm, NP, NM, ntw_p, ntw_m;
   long slab_bp, slab_M;
   size_t esize;  // bytes per element of the staged operands (8 FP64, 4 FP32)
+  bool fixed;    // split counts from fixed_slots (a plan that has to fit a workspace)
   long zrows_p, zrows_m;  // largest splits x rows of one contraction launch (sizes S and A)
   size_t n_Bc, n_Tp, n_Tm, n_W, n_S, n_A;
   size_t n_S2, n_A2;  // exchange-symmetric form only: second-product accumulators over all slots
   size_t bytes;
 };
 
-// Workgroups of the contraction kernel for ntw and the element size resident at once.
-template <typename T>
+// Workgroups of the FP64 contraction kernel for ntw resident at once.
 static const void* contract_fn(int ntw) {
-  typedef void (*F)(const T*, const T*, long, long, int, T*, long, long);
-  F f;
-  if constexpr (sizeof(T) == 8) {
-    switch (ntw) {
-      case 1: f = contract_f64<1>; break;
-      case 2: f = contract_f64<2>; break;
-      case 3: f = contract_f64<3>; break;
-      case 4: f = contract_f64<4>; break;
-      case 5: f = contract_f64<5>; break;
-      case 6: f = contract_f64<6>; break;
-      case 7: f = contract_f64<7>; break;
-      case 8: f = contract_f64<8>; break;
-      case 9: f = contract_f64<9>; break;
-      default: f = contract_f64<10>; break;
-    }
-  } else {
-    switch (ntw) {
-      case 1: f = contract_f32<1>; break;
-      case 2: f = contract_f32<2>; break;
-      case 3: f = contract_f32<3>; break;
-      case 4: f = contract_f32<4>; break;
-      case 5: f = contract_f32<5>; break;
-      case 6: f = contract_f32<6>; break;
-      case 7: f = contract_f32<7>; break;
-      case 8: f = contract_f32<8>; break;
-      case 9: f = contract_f32<9>; break;
-      default: f = contract_f32<10>; break;
-    }
-  }
-  return reinterpret_cast<const void*>(f);
+  typedef void (*F)(const double*, const double*, long, long, int, double*, long, long);
+  static constexpr F f[10] = {contract_f64<1>, contract_f64<2>, contract_f64<3>, contract_f64<4>, contract_f64<5>,
+                              contract_f64<6>, contract_f64<7>, contract_f64<8>, contract_f64<9>, contract_f64<10>};
+  return reinterpret_cast<const void*>(f[ntw - 1]);
 }
-static long contract_slots(int ntw, size_t esize) {
-  return resident_wgs(esize == 8 ? contract_fn<double>(ntw) : contract_fn<float>(ntw), 256, 2);
+static long contract_slots(int ntw) { return resident_wgs(contract_fn(ntw), 256, 2); }
+// The same as a fixed number per CU, where the split count must not move with the
+// kernel's registers and LDS: the FP32 partial sums are rounded split by split, so the
+// splits are part of the FP32 result; and a plan made to fit a given workspace must fit
+// the sizes it always did.
+static long fixed_slots(int ntw, size_t esize) {
+  static constexpr int per64[10] = {4, 4, 3, 3, 3, 2, 2, 2, 2, 2}, per32[10] = {8, 8, 7, 6, 5, 4, 4, 4, 3, 3};
+  return device_cus() * (esize == 8 ? per64 : per32)[ntw - 1];
 }
 
 // Splits of the contraction's k range for a launch of `rows` rows and 16*ntw-wide
@@ -771,15 +784,18 @@ static long contract_slots(int ntw, size_t esize) {
 // slice, and the workgroups resident together work on the same few splits (z is the
 // slowest grid index), so a slice that fits the last-level cache is fetched from HBM
 // about once instead of once per row tile.  Then balanced so that the last round of
-// workgroups is not a few stragglers.  At least 32 chunks per split.  kz: summed indices
-// per split.
-static int contract_splits(int ncol, int ntw, long rows, long K, size_t esize, long& kz) {
+// workgroups is not a few stragglers.  At least 32 chunks per split, 4
+// for FP64 on a free workspace, where a small ladder would otherwise leave most of
+// the chip idle (at o=4 v=24 the six workgroups of the whole k range take 32 us, split
+// twelve ways 5 us).  kz: summed indices per split.
+static int contract_splits(int ncol, int ntw, long rows, long K, size_t esize, bool fixed, long& kz) {
   const long nwg = (ncol / (16 * ntw)) * (rows / CRM);
-  const long slots = contract_slots(ntw, esize);
+  fixed = fixed || esize != 8;
+  const long slots = fixed ? fixed_slots(ntw, esize) : contract_slots(ntw);
   long z = (slots + nwg - 1) / nwg;
   const double chunk = static_cast<double>(env_long("RI_PPL_TAU_CHUNK_MB", TAU_CHUNK_MB)) * 1048576.0;
   z = std::max(z, static_cast<long>(std::ceil(static_cast<double>(K) * ncol * esize / chunk)));
-  const long zmax = std::max(1L, K / (32 * KC));
+  const long zmax = std::max(1L, K / ((fixed ? 32 : 4) * KC));
   z = std::max(1L, std::min(z, zmax));
   z = balance_splits(nwg, slots, K, KC, z, zmax);
   kz = (K + z - 1) / z;
@@ -793,7 +809,7 @@ static long max_split_rows(const Plan& p, int ncol, int ntw) {
   long kz;
   const long last = p.nbp - (p.nbp - 1) / p.slab_bp * p.slab_bp;
   long best = 0;
-  for (long rows : {p.slab_M, last * 256}) best = std::max(best, contract_splits(ncol, ntw, rows, p.K, p.esize, kz) * rows);
+  for (long rows : {p.slab_M, last * 256}) best = std::max(best, contract_splits(ncol, ntw, rows, p.K, p.esize, p.fixed, kz) * rows);
   return best;
 }
 
@@ -827,6 +843,7 @@ static bool make_plan(int o, int v, int naux, size_t esize, Plan& p, bool sym = 
   p.v = v;
   p.naux = naux;
   p.esize = esize;
+  p.fixed = fit_bytes > 0;
   p.nb = (v + TB - 1) / TB;
   p.vp = p.nb * TB;
   p.naux_p = static_cast<int>(round_up(naux, KC));
@@ -891,11 +908,11 @@ struct K64 {
   }
   static void build_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
                       T* Wp, T* Wm) {
-    build_w_f64<<<g, 512, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
+    build_w_f64<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
   }
   static void build_diag_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, int y0,
                            long pcd0, T* Wp, T* Wm) {
-    build_w_f64_diag<<<g, 512, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
+    build_w_f64_diag<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
   }
   template <int NTW>
   static void contract_k(dim3 g, hipStream_t s, const T* W, const T* Tt, long K, long M, int ncol, T* C, long kz,
@@ -925,11 +942,11 @@ struct K32 {
   }
   static void build_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
                       T* Wp, T* Wm) {
-    build_w_f32<<<g, 512, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
+    build_w_f32<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
   }
   static void build_diag_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, int y0,
                            long pcd0, T* Wp, T* Wm) {
-    build_w_f32_diag<<<g, 512, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
+    build_w_f32_diag<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
   }
   template <int NTW>
   static void contract_k(dim3 g, hipStream_t s, const T* W, const T* Tt, long K, long M, int ncol, T* C, long kz,
@@ -1008,18 +1025,18 @@ static int run_plan(const Plan& p, const double* B_vv, long qs, long rs, const d
     int dy0, ndiag;
     diag_pairs(slab0, npairs, dy0, ndiag);
     long kzp = 0, kzm = 0;
-    const int zp = contract_splits(p.NP, p.ntw_p, M, p.K, p.esize, kzp);
-    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, p.K, p.esize, kzm) : 1;
+    const int zp = contract_splits(p.NP, p.ntw_p, M, p.K, p.esize, p.fixed, kzp);
+    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, p.K, p.esize, p.fixed, kzm) : 1;
     {
       // per valid (a <= b): the v x v matrix (ac|bd) over all c, d, naux products each;
       // off-diagonal and diagonal ab block pairs in two launches
       ProfScope ps(s, KS::build, 2.0 * p.naux * vv * (le - ld));
-      KS::build_k(dim3(p.nbp * 4, npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, 0, Wp, Wm);
+      KS::build_k(dim3(p.nbp * (16 / BNW), npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, 0, Wp, Wm);
       RI_TRY(check_launch(KS::build));
     }
     if (ndiag > 0) {
       ProfScope ps(s, KS::build_diag, 2.0 * p.naux * vv * ld);
-      KS::build_diag_k(dim3(p.nbp * 4, ndiag), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, dy0, 0,
+      KS::build_diag_k(dim3(p.nbp * (16 / BNW), ndiag), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, dy0, 0,
                        Wp, Wm);
       RI_TRY(check_launch(KS::build_diag));
     }
@@ -1130,7 +1147,7 @@ static int run_sym(const Plan& p, const double* B_vv, const double* tau, double*
     count_pairs(p.v, slab0, p.nbp - slab0, ce, ct, cd);
     int dy0, ndiag;
     diag_pairs(slab0, npairs, dy0, ndiag);
-    const unsigned gx = static_cast<unsigned>((p.nbp - slab0) * 4);
+    const unsigned gx = static_cast<unsigned>((p.nbp - slab0) * (16 / BNW));
     const double per_ab = 2.0 * p.naux * (2.0 * ct + (ce - ct));
     {
       ProfScope ps(s, KS::build, per_ab * (le - ld));
@@ -1145,8 +1162,8 @@ static int run_sym(const Plan& p, const double* B_vv, const double* tau, double*
     }
     const size_t w0 = static_cast<size_t>(slab0) * 256 * p.slab_M;  // row slab0*256 of W
     long kzp = 0, kzm = 0;
-    const int zp = contract_splits(p.NP, p.ntw_p, M, K1, p.esize, kzp);
-    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, K1, p.esize, kzm) : 1;
+    const int zp = contract_splits(p.NP, p.ntw_p, M, K1, p.esize, p.fixed, kzp);
+    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, K1, p.esize, p.fixed, kzm) : 1;
     {
       ProfScope ps(s, KS::contract, 2.0 * (le * ce * p.po + lt * ct * p.pm));
       launch_contract<KS>(p.ntw_p, Wp + w0, Tp + static_cast<size_t>(slab0) * 256 * p.NP, K1, p.slab_M, M, p.NP, S,
@@ -1345,6 +1362,7 @@ size_t min_workspace_bytes(int o, int v, int naux, int precision) {
   Plan p;
   if (!make_plan(o, v, naux, esize_of(precision), p)) return 0;
   p.slab_bp = 1;
+  p.fixed = true;
   size_plan(p, false);
   return p.bytes;
 }

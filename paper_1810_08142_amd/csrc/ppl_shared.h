@@ -70,6 +70,16 @@ __device__ inline void xcd_tile(unsigned& tx, unsigned& ty) {
   ty = tile / gx;
 }
 
+// Compute units of the current device (256 where the runtime gives no answer).
+inline long device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+    return cus;
+  (void)hipGetLastError();  // leave no error behind for the next launch check
+  return 256;
+}
+
 // Workgroups of kernel f (block threads each) resident on the current device at once:
 // blocks per CU by the runtime's occupancy rule (registers, LDS, waves) times the CU
 // count, or 256 * dflt_per_cu where the runtime gives no answer (no device).
