@@ -481,7 +481,7 @@ __device__ __forceinline__ void contract_body(const T* __restrict__ W, const T* 
       }
 }
 template <int NTW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_f64(const double* __restrict__ W, const double* __restrict__ Tt,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract_f64(const double* __restrict__ W, const double* __restrict__ Tt,
                                                     long K, long M, int ncol, double* __restrict__ C, long kz,
                                                     long zs) {
   contract_body<double, NTW>(W, Tt, K, M, ncol, C, kz, zs);
@@ -603,13 +603,13 @@ __device__ __forceinline__ void contract_rows_body(const T* __restrict__ W, long
       }
 }
 template <int NTW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_rows_f64(const double* __restrict__ W, long ldw,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract_rows_f64(const double* __restrict__ W, long ldw,
                                                          const double* __restrict__ Tt, long M, int ncol,
                                                          double* __restrict__ C, int accum) {
   contract_rows_body<double, NTW>(W, ldw, Tt, M, ncol, C, accum);
 }
 template <int NTW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void contract_rows_f32(const float* __restrict__ W, long ldw,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract_rows_f32(const float* __restrict__ W, long ldw,
                                                          const float* __restrict__ Tt, long M, int ncol,
                                                          float* __restrict__ C, int accum) {
   contract_rows_body<float, NTW>(W, ldw, Tt, M, ncol, C, accum);
