@@ -34,6 +34,12 @@ size_t scratch_doubles(const GemmDesc& g, int batch);
 int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipStream_t s,
         int prec = RI_PREC_FP64);
 
+// The contraction g `count` times over in one launch: entry z reads A at g.a + items[3z], B
+// at g.b + items[3z + 1] and writes C at g.c + items[3z + 2] (items on the device, offsets
+// in doubles, those of A and B even).  Both operands k-contiguous and 16-byte aligned, K3 a
+// multiple of 16 (RI_E_ARG otherwise).
+int run_items(const GemmDesc& g, int count, const long* items, hipStream_t s);
+
 }  // namespace gemm
 
 // An FP64 tensor view on the device: dims with element strides (row-major when

@@ -582,6 +582,175 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #undef B_ROW
 #undef B_K
 
+// One 16-byte global load per lane straight into LDS, lane l of the wave to dst + 16 l bytes
+// (dst uniform over the wave); counted by vmcnt alone.
+__device__ __forceinline__ void load_lds16(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
+// The FP64 large tiles where both operands come in aligned 16-byte pieces (dma_ok): the
+// same 128 x 128 tile, loaded straight to LDS, a chunk ahead.  Every vector instruction
+// beside the products takes issue time from the matrix pipe (twelve per FP64 MFMA cost it
+// a third of its rate), and staging through registers spent some 120 per 64 products on
+// addresses, edge selects and LDS stores; here it is eight loads and their addresses.  A
+// k-contiguous operand is kept as rows of 16 k, its 16-byte pieces u at u ^ ((row / 2) & 7)
+// (the sixteen rows of one operand read then lie in distinct banks); the other as 16 rows
+// of 128.  Rows past the edge read the last one; their results are dropped.  Two buffers,
+// one barrier per chunk; the second workgroup of the CU fills the gaps.
+// grid (ceil(N/128), ceil(M/128), batch * splits); items: per batch entry the offsets of A, B
+// and C (NULL: the description's batch strides); splits as in gemm_mid.
+// At M = N = K = 16384 (o=32 v=512) 125 ms, 70 TFLOP/s (139 ms through registers).
+template <int AK, int BK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma(
+    GemmArgs g, const long* __restrict__ items, int splits, long cper, double* __restrict__ part) {
+  constexpr int OP = BL * KC;  // doubles of one operand's chunk
+  __shared__ double lds[2 * 2 * OP];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(w);
+  const long bm = static_cast<long>(blockIdx.y) * BL, bn = static_cast<long>(blockIdx.x) * BL;
+  const long zb = blockIdx.z / splits, zs = blockIdx.z % splits;
+  const double* A = g.a + (items ? items[3 * zb] : zb * g.a_batch);
+  const double* B = g.b + (items ? items[3 * zb + 1] : zb * g.b_batch);
+  double* C = g.c + (items ? items[3 * zb + 2] : zb * g.c_batch);
+
+  // 16-byte piece t + 256 r of an operand's chunk: k-contiguous: row t/8 + 32 r, piece t%8
+  // (the one stored there: t%8 ^ (row/2)&7, which does not depend on r); else rows
+  // 2 (t%64), +1 at k = t/64 + 4 r
+  const double *pa[4], *pb[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int u = (t & 7) ^ ((t >> 4) & 7), k = (t >> 6) + 4 * r;
+    const long ma = AK ? std::min(bm + (t >> 3) + 32 * r, g.M - 1) : std::min(bm + 2 * (t & 63), g.M - 2);
+    const long nb = BK ? std::min(bn + (t >> 3) + 32 * r, g.N - 1) : std::min(bn + 2 * (t & 63), g.N - 2);
+    pa[r] = A + g.a_row(ma) + (AK ? 2 * u : k * g.ak3);
+    pb[r] = B + g.b_col(nb) + (BK ? 2 * u : k * g.bk3);
+  }
+  // position of the next chunk to load
+  const long c_lo = zs * cper, nchunks = std::min(g.K / KC, c_lo + cper) - c_lo;
+  long k1, k2, k3;
+  div_mod(g.dK3, c_lo * KC, k1, k3);
+  div_mod(g.dK2, k1, k1, k2);
+  long ka = k1 * g.ak1 + k2 * g.ak2 + k3 * g.ak3, kb = k1 * g.bk1 + k2 * g.bk2 + k3 * g.bk3;
+  auto load = [&](int buf) {
+    double* d = lds + buf * 2 * OP;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      load_lds16(pa[r] + ka, d + (wv * 64 + 256 * r) * 2);
+      load_lds16(pb[r] + kb, d + OP + (wv * 64 + 256 * r) * 2);
+    }
+    k3 += KC;
+    ka += KC * g.ak3;
+    kb += KC * g.bk3;
+    if (k3 == g.K3) {
+      k3 = 0;
+      ka += g.ak2 - g.K3 * g.ak3;
+      kb += g.bk2 - g.K3 * g.bk3;
+      if (++k2 == g.K2) {
+        k2 = 0;
+        ka += g.ak1 - g.K2 * g.ak2;
+        kb += g.bk1 - g.K2 * g.bk2;
+      }
+    }
+  };
+  double4_t acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
+  const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
+  const int l16 = lane & 15, kq = lane >> 4;
+  // operand element (row l16, k = 4 s + kq) of a 16-row tile, relative to the tile
+  auto at = [&](int kc, int s) {
+    return kc ? l16 * KC + 2 * ((2 * s + (kq >> 1)) ^ (l16 >> 1)) + (kq & 1) : (4 * s + kq) * BL + l16;
+  };
+  double fa[2][4], fb[2][4];
+  auto fread = [&](int q, int buf, int s) {
+    const double* sa = lds + buf * 2 * OP + wm * (AK ? KC : 1) + at(AK, s);
+    const double* sb = lds + buf * 2 * OP + OP + wn * (BK ? KC : 1) + at(BK, s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      fa[q][i] = sa[16 * i * (AK ? KC : 1)];
+      fb[q][i] = sb[16 * i * (BK ? KC : 1)];
+    }
+  };
+  load(0);
+  for (long ch = 0; ch < nchunks; ++ch) {
+    const int buf = ch & 1;
+    // this chunk has landed and every wave is past its reads of the other buffer
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (ch + 1 < nchunks) load(buf ^ 1);
+    fread(0, buf, 0);
+#pragma unroll
+    for (int s = 0; s < KC / 4; ++s) {
+      if (s + 1 < KC / 4) fread((s + 1) & 1, buf, s + 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s & 1][i], fb[s & 1][j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const long n = bn + wn + 16 * j + l16;
+    if (n >= g.N) continue;
+    double* col = C + g.c_col(n);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const long m = bm + wm + 16 * i + 4 * r + kq;
+        if (m >= g.M) continue;
+        if (splits > 1)
+          part[(zs * g.M + m) * g.N + n] = acc[i][j][r];
+        else
+          put(g, col + g.c_row(m), acc[i][j][r]);
+      }
+  }
+}
+
+// Whether every 16-byte piece gemm_dma loads is aligned and inside the operand: pairs run
+// along k (k-contiguous: all other strides even) or along the rows (rows contiguous in
+// pairs: an even innermost extent, all other strides even).
+static bool dma_ok(const void* p, int kfast, long rows2, long r1, long r2, long k1, long k2, long k3, long batch) {
+  if (reinterpret_cast<uintptr_t>(p) & 15) return false;
+  if ((r1 | k1 | k2 | batch) & 1) return false;
+  return kfast ? k3 == 1 && r2 % 2 == 0 : r2 == 1 && rows2 % 2 == 0 && k3 % 2 == 0;
+}
+
+static bool dma_ok(const GemmDesc& g, int batch, int a_kfast, int b_kfast) {
+  return g.K3 % KC == 0 &&
+         dma_ok(g.a, a_kfast, g.M2, g.am1, g.am2, g.ak1, g.ak2, g.ak3, batch > 1 ? g.a_batch : 0) &&
+         dma_ok(g.b, b_kfast, g.N2, g.bn1, g.bn2, g.bk1, g.bk2, g.bk3, batch > 1 ? g.b_batch : 0);
+}
+
+template <int AK, int BK>
+static void launch_dma_k(const GemmArgs& ga, int batch, const long* items, int splits, long cper, double* part,
+                         hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>((ga.N + BL - 1) / BL), static_cast<unsigned>((ga.M + BL - 1) / BL),
+                  static_cast<unsigned>(batch * splits));
+  gemm_dma<AK, BK><<<grid, 256, 0, s>>>(ga, items, splits, cper, part);
+}
+static void launch_dma(const GemmArgs& ga, int batch, int a_kfast, int b_kfast, int splits, long cper, double* part,
+                       hipStream_t s) {
+  if (a_kfast && b_kfast) launch_dma_k<1, 1>(ga, batch, nullptr, splits, cper, part, s);
+  else if (a_kfast) launch_dma_k<1, 0>(ga, batch, nullptr, splits, cper, part, s);
+  else if (b_kfast) launch_dma_k<0, 1>(ga, batch, nullptr, splits, cper, part, s);
+  else launch_dma_k<0, 0>(ga, batch, nullptr, splits, cper, part, s);
+}
+
+int run_items(const GemmDesc& g, int count, const long* items, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0 || count <= 0) return RI_OK;
+  if (g.K <= 0 || !dma_ok(g, 1, 1, 1)) {
+    set_error("gemm items: operands must be k-contiguous and aligned, K a multiple of %d", KC);
+    return RI_E_ARG;
+  }
+  launch_dma_k<1, 1>(make_args(g), count, items, 1, g.K / KC, nullptr, s);
+  return check_launch("gemm_dma");
+}
+
 // C(m, n) = alpha * sum_z part[z][m][n] + beta * C(m, n), z in order
 __global__ void split_reduce(GemmArgs g, int splits, const double* __restrict__ part) {
   const long idx = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -594,10 +763,12 @@ __global__ void split_reduce(GemmArgs g, int splits, const double* __restrict__ 
 
 // How a contraction that the large tiles do not take is run.
 struct Choice {
-  bool small;   // gemm_small (nw waves per tile), else gemm_mid
+  bool small;   // gemm_small (nw waves per tile), else
+  bool dma;     // gemm_dma split over k, else gemm_mid
   bool uni;     // gemm_mid's chunks run along the innermost summed level
   int nw, splits;
-  long per;     // per split: summed indices (small) or chunks (mid)
+  long per;     // per split: summed indices (small) or chunks (dma, mid)
+  int a_kfast, b_kfast;
 };
 
 // Small tiles where 64 x 64 ones, split over k or not, would not give every CU one, or
@@ -607,11 +778,25 @@ struct Choice {
 // CUs a tile as they are (1000 x 1000 x 1000: 74 us whole, 64 us in two splits and 14 us
 // to add them).  Partials take at most 2^26 doubles.  The contractions of a residual at
 // o=10 v=100 naux=300 take 1.09 ms (1.67 ms with 64 x 64 tiles of four waves throughout).
+// The 128 x 128 tiles loaded straight to LDS come first where splitting k gives them a
+// workgroup per CU, at least 32 chunks each (1024 x 1024 over 262144 summed indices: 14.2 ms
+// in 64 x 64 tiles, 8.5 ms so).
 static Choice choose(const GemmDesc& g, int batch) {
   Choice c{};
+  // consecutive threads walk k when the innermost k stride is 1 and the m/n stride is not
+  c.a_kfast = (g.ak3 == 1 && g.K3 >= 4 && g.am2 != 1) ? 1 : 0;
+  c.b_kfast = (g.bk3 == 1 && g.K3 >= 4 && g.bn2 != 1) ? 1 : 0;
   const long tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const long tiles_s = ((g.M + SM - 1) / SM) * ((g.N + SM - 1) / SM) * batch;
   const long cap = std::max(1L, (1L << 26) / (g.M * g.N));
+  const long tiles_l = ((g.M + BL - 1) / BL) * ((g.N + BL - 1) / BL);
+  const long z_l = std::min({512 / tiles_l, g.K / (32 * KC), cap});
+  if (batch == 1 && std::min(g.M, g.N) >= BL && tiles_l * z_l >= 256 && dma_ok(g, 1, c.a_kfast, c.b_kfast)) {
+    c.dma = true;
+    c.per = (g.K / KC + z_l - 1) / z_l;
+    c.splits = static_cast<int>((g.K / KC + c.per - 1) / c.per);
+    return c;
+  }
   const long full = 16L * KC;  // the least k range of a mid split
   c.small = tiles * batch * std::max(1L, batch > 1 ? 1 : std::min(g.K / full, cap)) < 256 || std::min(g.M, g.N) <= SM;
   if (c.small) {
@@ -646,9 +831,8 @@ int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipSt
     return RI_E_ARG;
   }
   const GemmArgs ga = make_args(g);
-  // consecutive threads walk k when the innermost k stride is 1 and the m/n stride is not
-  const int a_kfast = (g.ak3 == 1 && g.K3 >= 4 && g.am2 != 1) ? 1 : 0;
-  const int b_kfast = (g.bk3 == 1 && g.K3 >= 4 && g.bn2 != 1) ? 1 : 0;
+  Choice c = choose(g, batch);
+  const int a_kfast = c.a_kfast, b_kfast = c.b_kfast;
   // large tiles when they still give the chip a few workgroups per CU
   // (RI_GEMM_LARGE_MIN_TILES overrides the threshold, e.g. to test the path at small sizes)
   const char* env = getenv("RI_GEMM_LARGE_MIN_TILES");
@@ -663,6 +847,8 @@ int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipSt
       else if (a_kfast) gemm_large<float, 1, 0><<<grid, 256, 0, s>>>(ga);
       else if (b_kfast) gemm_large<float, 0, 1><<<grid, 256, 0, s>>>(ga);
       else gemm_large<float, 0, 0><<<grid, 256, 0, s>>>(ga);
+    } else if (dma_ok(g, batch, a_kfast, b_kfast)) {
+      launch_dma(ga, batch, a_kfast, b_kfast, 1, g.K / KC, nullptr, s);
     } else {
       if (a_kfast && b_kfast) gemm_large<double, 1, 1><<<grid, 256, 0, s>>>(ga);
       else if (a_kfast) gemm_large<double, 1, 0><<<grid, 256, 0, s>>>(ga);
@@ -671,13 +857,14 @@ int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipSt
     }
     return check_launch("gemm_large");
   }
-  Choice c = choose(g, batch);
   if (c.splits > 1 && !(scratch && scratch_len >= static_cast<size_t>(c.splits) * g.M * g.N)) {
     c.splits = 1;
     c.per = g.K;  // at least as many chunks
   }
   const int splits = c.splits;
-  if (c.small) {
+  if (c.dma) {
+    launch_dma(ga, 1, a_kfast, b_kfast, splits, c.per, scratch, s);
+  } else if (c.small) {
     const long tm = (g.M + SM - 1) / SM, tn = (g.N + SM - 1) / SM;
     const dim3 grid(static_cast<unsigned>(tm * tn), 1, static_cast<unsigned>(batch * splits));
     if (c.nw == 16) gemm_small<16><<<grid, 1024, 0, s>>>(ga, static_cast<int>(tn), splits, c.per, scratch);
