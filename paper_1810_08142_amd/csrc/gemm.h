@@ -34,11 +34,13 @@ size_t scratch_doubles(const GemmDesc& g, int batch);
 int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipStream_t s,
         int prec = RI_PREC_FP64);
 
-// The contraction g `count` times over in one launch: entry z reads A at g.a + items[3z], B
-// at g.b + items[3z + 1] and writes C at g.c + items[3z + 2] (items on the device, offsets
-// in doubles, those of A and B even).  Both operands k-contiguous and 16-byte aligned, K3 a
-// multiple of 16 (RI_E_ARG otherwise).
-int run_items(const GemmDesc& g, int count, const long* items, hipStream_t s);
+// C = alpha * (A1 B1 + A2 B2) + beta * C, `count` times over in one launch: entry z takes its
+// operands at g.a + items[5z], g.b + items[5z + 1], g.a + items[5z + 2], g.b + items[5z + 3]
+// and writes g.c + items[5z + 4] (items on the device, offsets in doubles, those of A and B
+// even); both products have g's extents and strides, but A2's two row levels are exchanged:
+// its row (m1, m2) is at m2 * am1 + m1 * am2.  Both operands k-contiguous and 16-byte
+// aligned, K3 a multiple of 16 (RI_E_ARG otherwise).
+int run_pairs(const GemmDesc& g, int count, const long* items, hipStream_t s);
 
 }  // namespace gemm
 

@@ -82,6 +82,11 @@ struct GemmArgs : GemmDesc {
     div_mod(dM2, m, q, r);
     return q * am1 + r * am2;
   }
+  __device__ long a_row_exchanged(long m) const {
+    long q, r;
+    div_mod(dM2, m, q, r);
+    return r * am1 + q * am2;
+  }
   __device__ long c_row(long m) const {
     long q, r;
     div_mod(dM2, m, q, r);
@@ -598,10 +603,12 @@ __device__ __forceinline__ void load_lds16(const void* src, void* dst) {
 // (the sixteen rows of one operand read then lie in distinct banks); the other as 16 rows
 // of 128.  Rows past the edge read the last one; their results are dropped.  Two buffers,
 // one barrier per chunk; the second workgroup of the CU fills the gaps.
-// grid (ceil(N/128), ceil(M/128), batch * splits); items: per batch entry the offsets of A, B
-// and C (NULL: the description's batch strides); splits as in gemm_mid.
+// grid (ceil(N/128), ceil(M/128), batch * splits); splits as in gemm_mid.
+// PAIR: batch entry z computes C = A1 B1 + A2 B2 with the two levels of A2's rows exchanged
+// (row (m1, m2) of A2 at m2 am1 + m1 am2); items: per entry the offsets of A1, B1, A2, B2
+// and C.  The summed index runs over the first product, then the second.
 // At M = N = K = 16384 (o=32 v=512) 125 ms, 70 TFLOP/s (139 ms through registers).
-template <int AK, int BK>
+template <int AK, int BK, bool PAIR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma(
     GemmArgs g, const long* __restrict__ items, int splits, long cper, double* __restrict__ part) {
   constexpr int OP = BL * KC;  // doubles of one operand's chunk
@@ -610,24 +617,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wv = __builtin_amdgcn_readfirstlane(w);
   const long bm = static_cast<long>(blockIdx.y) * BL, bn = static_cast<long>(blockIdx.x) * BL;
   const long zb = blockIdx.z / splits, zs = blockIdx.z % splits;
-  const double* A = g.a + (items ? items[3 * zb] : zb * g.a_batch);
-  const double* B = g.b + (items ? items[3 * zb + 1] : zb * g.b_batch);
-  double* C = g.c + (items ? items[3 * zb + 2] : zb * g.c_batch);
+  if constexpr (PAIR) items += 5 * zb;
+  const double* A = g.a + (PAIR ? items[0] : zb * g.a_batch);
+  const double* B = g.b + (PAIR ? items[1] : zb * g.b_batch);
+  double* C = g.c + (PAIR ? items[4] : zb * g.c_batch);
 
   // 16-byte piece t + 256 r of an operand's chunk: k-contiguous: row t/8 + 32 r, piece t%8
   // (the one stored there: t%8 ^ (row/2)&7, which does not depend on r); else rows
   // 2 (t%64), +1 at k = t/64 + 4 r
   const double *pa[4], *pb[4];
+  auto set_rows = [&](bool second) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int u = (t & 7) ^ ((t >> 4) & 7), k = (t >> 6) + 4 * r;
-    const long ma = AK ? std::min(bm + (t >> 3) + 32 * r, g.M - 1) : std::min(bm + 2 * (t & 63), g.M - 2);
-    const long nb = BK ? std::min(bn + (t >> 3) + 32 * r, g.N - 1) : std::min(bn + 2 * (t & 63), g.N - 2);
-    pa[r] = A + g.a_row(ma) + (AK ? 2 * u : k * g.ak3);
-    pb[r] = B + g.b_col(nb) + (BK ? 2 * u : k * g.bk3);
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int u = (t & 7) ^ ((t >> 4) & 7), k = (t >> 6) + 4 * r;
+      const long ma = AK ? std::min(bm + (t >> 3) + 32 * r, g.M - 1) : std::min(bm + 2 * (t & 63), g.M - 2);
+      const long nb = BK ? std::min(bn + (t >> 3) + 32 * r, g.N - 1) : std::min(bn + 2 * (t & 63), g.N - 2);
+      pa[r] = A + (PAIR && second ? g.a_row_exchanged(ma) : g.a_row(ma)) + (AK ? 2 * u : k * g.ak3);
+      pb[r] = B + g.b_col(nb) + (BK ? 2 * u : k * g.bk3);
+    }
+  };
+  set_rows(false);
   // position of the next chunk to load
-  const long c_lo = zs * cper, nchunks = std::min(g.K / KC, c_lo + cper) - c_lo;
+  const long c_lo = zs * cper, nchunks = PAIR ? 2 * g.K / KC : std::min(g.K / KC, c_lo + cper) - c_lo;
   long k1, k2, k3;
   div_mod(g.dK3, c_lo * KC, k1, k3);
   div_mod(g.dK2, k1, k1, k2);
@@ -677,6 +688,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   load(0);
   for (long ch = 0; ch < nchunks; ++ch) {
     const int buf = ch & 1;
+    if (PAIR && ch + 1 == g.K / KC) {  // the next chunk is the second product's first
+      A = g.a + items[2];
+      B = g.b + items[3];
+      set_rows(true);
+      k2 = k3 = ka = kb = 0;
+    }
     // this chunk has landed and every wave is past its reads of the other buffer
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (ch + 1 < nchunks) load(buf ^ 1);
@@ -726,12 +743,12 @@ static bool dma_ok(const GemmDesc& g, int batch, int a_kfast, int b_kfast) {
          dma_ok(g.b, b_kfast, g.N2, g.bn1, g.bn2, g.bk1, g.bk2, g.bk3, batch > 1 ? g.b_batch : 0);
 }
 
-template <int AK, int BK>
+template <int AK, int BK, bool PAIR = false>
 static void launch_dma_k(const GemmArgs& ga, int batch, const long* items, int splits, long cper, double* part,
                          hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((ga.N + BL - 1) / BL), static_cast<unsigned>((ga.M + BL - 1) / BL),
                   static_cast<unsigned>(batch * splits));
-  gemm_dma<AK, BK><<<grid, 256, 0, s>>>(ga, items, splits, cper, part);
+  gemm_dma<AK, BK, PAIR><<<grid, 256, 0, s>>>(ga, items, splits, cper, part);
 }
 static void launch_dma(const GemmArgs& ga, int batch, int a_kfast, int b_kfast, int splits, long cper, double* part,
                        hipStream_t s) {
@@ -741,13 +758,13 @@ static void launch_dma(const GemmArgs& ga, int batch, int a_kfast, int b_kfast, 
   else launch_dma_k<0, 0>(ga, batch, nullptr, splits, cper, part, s);
 }
 
-int run_items(const GemmDesc& g, int count, const long* items, hipStream_t s) {
+int run_pairs(const GemmDesc& g, int count, const long* items, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || count <= 0) return RI_OK;
-  if (g.K <= 0 || !dma_ok(g, 1, 1, 1)) {
-    set_error("gemm items: operands must be k-contiguous and aligned, K a multiple of %d", KC);
+  if (g.K <= 0 || !dma_ok(g, 1, 1, 1) || g.am1 % 2) {
+    set_error("gemm pairs: operands must be k-contiguous and aligned, K a multiple of %d", KC);
     return RI_E_ARG;
   }
-  launch_dma_k<1, 1>(make_args(g), count, items, 1, g.K / KC, nullptr, s);
+  launch_dma_k<1, 1, true>(make_args(g), count, items, 1, 0, nullptr, s);
   return check_launch("gemm_dma");
 }
 

@@ -16,12 +16,15 @@
 // so the energy kernel evaluates it for each distinct ordering (i', j', k') from the
 // one W and V, reading them through permuted tiles.
 //
-// Per triplet: six GEMMs on the library's MFMA engine (FP64 or FP32), one per term of P, each
-// writing its term in its own natural layout (contiguous output rows; the o-sized sum
-// of a term rides along as extra columns of the summed index), a tiled kernel
-// symmetrises the six into W and forms V = W + the t1 terms, and a tiled kernel sums
-// the energy in a fixed order.  The GEMM operands (with (yd|xp) and (zr|ql) from the
-// RI factors) and (ia|jb) are built once.
+// Triplets are taken in batches.  The six terms of P come in pairs with one third virtual
+// z: X(p, q, r; x, y, z) and X(q, p, r; y, x, z), both [x][y][z] with a summed index of their
+// own, so each pair is one GEMM over the two summed indices one after the other (the second
+// A read with its rows (x, y) exchanged).  Per batch: one launch of three such GEMMs per
+// triplet on the library's MFMA engine (FP64 or FP32), each writing its pair's sum in its
+// own natural layout (contiguous output rows; the o-sized sum of a term rides along as extra
+// columns of the summed index), and one tiled kernel that symmetrises the three into W,
+// forms V = W + the t1 terms and sums the energy in a fixed order, all in LDS.  The GEMM
+// operands (with (yd|xp) and (zr|ql) from the RI factors) and (ia|jb) are built once.
 #include <cmath>
 #include <vector>
 
@@ -34,127 +37,148 @@ constexpr int TE = 8;  // tile edge of the energy kernel
 
 // element m of permutation p of (0, 1, 2): p in the order 012 021 102 120 201 210, the
 // 18 two-bit elements packed in that order
-__host__ __device__ inline int perm_at(int p, int m) {
-  constexpr unsigned long long table = 0x192261624ull;
-  return static_cast<int>((table >> (2 * (3 * p + m))) & 3ull);
+__host__ __device__ constexpr int perm_at(int p, int m) {
+  return static_cast<int>((0x192261624ull >> (2 * (3 * p + m))) & 3ull);
 }
-
-// One ordering (i', j', k') of the triplet and the tiles its four reads come from:
-// r1 for W'^{abc} (and V'^{abc}), r2 for W'^{bca}, r3 for W'^{cab}, r4 for V'^{cba}.
-struct Order {
-  int ip, jp, kp;
-  int r1, r2, r3, r4;
-};
-struct Orders {
-  int n;
-  Order t[6];
-};
-
-// W[a][b][c] = sum_p Y_p[y0][y1][y2] with y_m = (a, b, c)[perm(p, m)] (the six terms of
-// P, each computed in its own natural layout), and V = W + (jb|kc) t^a_i + (ia|kc) t^b_j
-// + (ia|jb) t^c_k.  Each block stages, term by term, the 8^3 tile of Y_p at the
-// permuted block coordinates in LDS and reads it transposed, so every global access
-// runs along c.  grid nt^3, block 512.
-__global__ __launch_bounds__(512) void assemble_wv(const double* __restrict__ Y, const double* __restrict__ K,
-                                                   const double* __restrict__ t1, int o, int v, int i, int j, int k,
-                                                   double* __restrict__ W, double* __restrict__ V) {
-  __shared__ double tile[TE][TE][TE];
-  const int nt = (v + TE - 1) / TE;
-  const long bid = blockIdx.x;
-  const int Z0 = static_cast<int>(bid / (static_cast<long>(nt) * nt)) * TE;
-  const int Z1 = static_cast<int>((bid / nt) % nt) * TE;
-  const int Z2 = static_cast<int>(bid % nt) * TE;
-  const int t = threadIdx.x, u = t >> 6, w = (t >> 3) & 7, z = t & 7;
-  auto Zof = [&](int m) { return m == 0 ? Z0 : (m == 1 ? Z1 : Z2); };
-  auto xl = [&](int m) { return m == 0 ? u : (m == 1 ? w : z); };
-  const long v3 = static_cast<long>(v) * v * v;
-  double acc = 0.0;
-  for (int p = 0; p < 6; ++p) {
-    const int y0 = Zof(perm_at(p, 0)) + u, y1 = Zof(perm_at(p, 1)) + w, y2 = Zof(perm_at(p, 2)) + z;
-    const bool in = y0 < v && y1 < v && y2 < v;
-    tile[u][w][z] = in ? Y[p * v3 + (static_cast<long>(y0) * v + y1) * v + y2] : 0.0;
-    __syncthreads();
-    acc += tile[xl(perm_at(p, 0))][xl(perm_at(p, 1))][xl(perm_at(p, 2))];
-    __syncthreads();
-  }
-  const int a = Z0 + u, b = Z1 + w, c = Z2 + z;
-  if (a < v && b < v && c < v) {
-    auto Kx = [&](int i1, int p1, int i2, int p2) { return K[((static_cast<long>(i1) * v + p1) * o + i2) * v + p2]; };
-    const long at = (static_cast<long>(a) * v + b) * v + c;
-    W[at] = acc;
-    V[at] = acc + Kx(j, b, k, c) * t1[i * v + a] + Kx(i, a, k, c) * t1[j * v + b] + Kx(i, a, j, b) * t1[k * v + c];
-  }
-}
-
 // index of the permutation (e0, e1, e2) in the order of perm_at
-__host__ __device__ inline int perm_index(int e0, int e1) { return 2 * e0 + (e1 > e0 ? e1 - 1 : e1); }
+__host__ __device__ constexpr int perm_index(int e0, int e1) { return 2 * e0 + (e1 > e0 ? e1 - 1 : e1); }
+// p o q: element m is element q(m) of p
+__host__ __device__ constexpr int perm_mul(int p, int q) {
+  return perm_index(perm_at(p, perm_at(q, 0)), perm_at(p, perm_at(q, 1)));
+}
+__host__ __device__ constexpr int perm_inv(int p) {
+  return perm_index(perm_at(p, 0) == 0 ? 0 : perm_at(p, 1) == 0 ? 1 : 2,
+                    perm_at(p, 0) == 1 ? 0 : perm_at(p, 1) == 1 ? 1 : 2);
+}
 
-// Energy of one triplet over the orderings in `ord`, summed per unordered triple of
-// 8-wide tiles {A, B, C} (A <= B <= C, packed in tiles[] as A | B << 10 | C << 20)
-// into part[block].  Each block stages the six orientations of its tile triple of W
-// and V in LDS (orientation p holds W[Z_p0 + u][Z_p1 + w][Z_p2 + z] for Z = (A, B, C)
-// in elements) and evaluates every distinct ordering s of the triple from them, so each
-// tile of W and V is read from memory once per triplet.  grid = number of tile
-// triples, block 512.
-__global__ __launch_bounds__(512) void energy_tiles(const double* __restrict__ W, const double* __restrict__ V,
-                                                    const double* __restrict__ eps, int o, int v, Orders ord,
-                                                    const int* __restrict__ tiles, double* __restrict__ part) {
-  __shared__ double tw[6][TE][TE][TE];
-  __shared__ double tv[6][TE][TE][TE];
-  __shared__ double red[512];
+// Energy of the triplets of a batch, W and V formed on the way.
+//
+//   W[a][b][c] = sum over p in {012, 021, 120} of Y_p[y0][y1][y2], y_m = (a, b, c)[perm(p, m)]
+//   (the three pair sums of P, each computed in its own natural layout),
+//   V = W + (jb|kc) t^a_i + (ia|kc) t^b_j + (ia|jb) t^c_k.
+//
+// One block per unordered triple of 8-wide tiles {A, B, C} (A <= B <= C, packed in tiles[]
+// as A | B << 10 | C << 20) and triplet.  It reads the 8^3 tiles of the three Y at the six
+// orientations (every element of Y once over the launch, 18 loads per thread issued
+// together), sums them through LDS (all global accesses run along the last index) and
+// keeps the six orientations of W and V there: orientation p holds W[Z_p0 + u][Z_p1 + w]
+// [Z_p2 + z] for Z = (A, B, C) in elements.  Then it evaluates every distinct ordering of
+// the tile triple: at (a, b, c) the six permuted elements of W and of V are read once and
+// serve all orderings (i', j', k') of the triplet, ordering x taking W'^{abc} from
+// permutation x^-1 and W'^{bca}, W'^{cab}, V'^{cba} from it followed by the relabelling.
+// LDS tiles have strides 73, 9, 1 (at most two lanes of a permuted read share a bank).
+// Bound by the read of Y (24 v^3 bytes a triplet); at o=12 v=120 a triplet takes 19.5 us
+// (assembling six terms and summing in two kernels with W and V in memory: 94 us).
+// part[blockIdx.y * gridDim.x + blockIdx.x].  grid (tile triples, triplets), block 512.
+constexpr int LS0 = 73, LS1 = 9, LT = 584;
+// the permutations whose natural layouts hold the pairs: 012, 021, 120
+__host__ __device__ constexpr int term(int p) { return p == 2 ? 3 : p; }
+struct Trip {
+  int i, j, k;
+};
+// Summand of one (a, b, c) over the distinct orderings of a triplet (i' = x(0)-th of i, j, k
+// and so on), from the permuted elements of W and V.  KIND: 1 for i == j, plus 2 for j == k;
+// of the permutations that give one ordering the first is taken.
+template <int KIND>
+__device__ inline double orderings(const double (&wv)[6], const double (&vv)[6]) {
+  double sum = 0.0;
+#pragma unroll
+  for (int x = 0; x < 6; ++x) {
+    if (KIND == 3 ? x > 0 : KIND == 1 ? perm_mul(2, x) < x : KIND == 2 ? perm_mul(1, x) < x : false) continue;
+    const int inv = perm_inv(x);
+    sum += (4.0 * wv[inv] + wv[perm_mul(3, inv)] + wv[perm_mul(4, inv)]) * (vv[inv] - vv[perm_mul(5, inv)]);
+  }
+  return sum;
+}
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void energy_tiles(
+    const double* __restrict__ Y, const double* __restrict__ K, const double* __restrict__ t1,
+    const double* __restrict__ eps, int o, int v, const Trip* __restrict__ trips, const int* __restrict__ tiles,
+    double* __restrict__ part) {
+  __shared__ double st[3 * LT];
+  __shared__ double tw[6 * LT];
+  __shared__ double tv[6 * LT];
   const int code = tiles[blockIdx.x];
   const int bt[3] = {code & 1023, (code >> 10) & 1023, (code >> 20) & 1023};
+  const Trip tr = trips[blockIdx.y];
+  const long v3 = static_cast<long>(v) * v * v;
+  Y += 3 * v3 * blockIdx.y;
   const int t = threadIdx.x, u = t >> 6, w = (t >> 3) & 7, z = t & 7;
-  auto Zof = [&](int m) { return (m == 0 ? bt[0] : (m == 1 ? bt[1] : bt[2])) * TE; };
-  for (int p = 0; p < 6; ++p) {
-    const int y0 = Zof(perm_at(p, 0)) + u, y1 = Zof(perm_at(p, 1)) + w, y2 = Zof(perm_at(p, 2)) + z;
-    const bool in = y0 < v && y1 < v && y2 < v;
-    const long at = (static_cast<long>(y0) * v + y1) * v + y2;
-    tw[p][u][w][z] = in ? W[at] : 0.0;
-    tv[p][u][w][z] = in ? V[at] : 0.0;
+  const int x[3] = {u, w, z};
+  // element of a Y tile: coordinate m of the thread in the block of virtuals bt[q]; past the
+  // edge the last element is read (never used)
+  int e[3][3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int m = 0; m < 3; ++m) e[q][m] = min(bt[q] * TE + x[m], v - 1);
+  int L[6];  // position of the thread's permuted coordinates in an LDS tile
+#pragma unroll
+  for (int p = 0; p < 6; ++p) L[p] = x[perm_at(p, 0)] * LS0 + x[perm_at(p, 1)] * LS1 + x[perm_at(p, 2)];
+  double y[6][3];  // [orientation][pair]
+#pragma unroll
+  for (int sg = 0; sg < 6; ++sg)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const int q = perm_mul(sg, term(p));
+      y[sg][p] = Y[p * v3 + (static_cast<long>(e[perm_at(q, 0)][0]) * v + e[perm_at(q, 1)][1]) * v + e[perm_at(q, 2)][2]];
+    }
+  auto Kx = [&](int i1, int p1, int i2, int p2) { return K[((static_cast<long>(i1) * v + p1) * o + i2) * v + p2]; };
+#pragma unroll
+  for (int sg = 0; sg < 6; ++sg) {
+    double acc = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) st[p * LT + L[0]] = y[sg][p];
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) acc += st[p * LT + L[term(p)]];
+    const int a = e[perm_at(sg, 0)][0], b = e[perm_at(sg, 1)][1], c = e[perm_at(sg, 2)][2];
+    tw[sg * LT + L[0]] = acc;
+    tv[sg * LT + L[0]] = acc + Kx(tr.j, b, tr.k, c) * t1[tr.i * v + a] + Kx(tr.i, a, tr.k, c) * t1[tr.j * v + b] +
+                         Kx(tr.i, a, tr.j, b) * t1[tr.k * v + c];
   }
   __syncthreads();
-  auto xl = [&](int m) { return m == 0 ? u : (m == 1 ? w : z); };  // local coordinate of a, b or c
+  const int kind = (tr.i == tr.j ? 1 : 0) + (tr.j == tr.k ? 2 : 0);
+  const double eo = eps[tr.i] + eps[tr.j] + eps[tr.k];
   double acc = 0.0;
+#pragma unroll
   for (int sg = 0; sg < 6; ++sg) {
     // skip an ordering of the tile triple that repeats an earlier one (equal tiles)
     const int k0 = bt[perm_at(sg, 0)], k1 = bt[perm_at(sg, 1)], k2 = bt[perm_at(sg, 2)];
     bool dup = false;
+#pragma unroll
     for (int s2 = 0; s2 < sg; ++s2)
       dup = dup || (bt[perm_at(s2, 0)] == k0 && bt[perm_at(s2, 1)] == k1 && bt[perm_at(s2, 2)] == k2);
     if (dup) continue;
     const int a = k0 * TE + u, b = k1 * TE + w, c = k2 * TE + z;
     if (a >= v || b >= v || c >= v) continue;
-    // element (a, b, c) of orientation sg; a read in orientation rho of (a, b, c) comes
-    // from tile sg o rho at local coordinates (x_rho0, x_rho1, x_rho2)
-    auto rd = [&](const double (*tt)[TE][TE][TE], int rho) {
-      const int r0 = perm_at(rho, 0), r1 = perm_at(rho, 1);
-      const int tau = perm_index(perm_at(sg, r0), perm_at(sg, r1));
-      return tt[tau][xl(r0)][xl(r1)][xl(perm_at(rho, 2))];
-    };
-    // D is symmetric in (i, j, k): one reciprocal serves every ordering
-    const double d = eps[ord.t[0].ip] + eps[ord.t[0].jp] + eps[ord.t[0].kp] - (eps[o + a] + eps[o + b] + eps[o + c]);
-    double sum = 0.0;
+    // element (a, b, c) of orientation sg; read through permutation p it comes from tile
+    // sg o p at the thread's coordinates permuted by p
+    double wv[6], vv[6];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      if (q >= ord.n) break;
-      const Order& r = ord.t[q];
-      sum += (4.0 * rd(tw, r.r1) + rd(tw, r.r2) + rd(tw, r.r3)) * (rd(tv, r.r1) - rd(tv, r.r4));
+    for (int p = 0; p < 6; ++p) {
+      wv[p] = tw[perm_mul(sg, p) * LT + L[p]];
+      vv[p] = tv[perm_mul(sg, p) * LT + L[p]];
     }
+    const double d = eo - (eps[o + a] + eps[o + b] + eps[o + c]);
+    const double sum = kind == 0 ? orderings<0>(wv, vv) : kind == 1 ? orderings<1>(wv, vv)
+                     : kind == 2 ? orderings<2>(wv, vv) : orderings<3>(wv, vv);
     acc += sum / (3.0 * d);
   }
-  red[t] = acc;
+  __syncthreads();  // the reduction reuses the staging tiles
+  st[t] = acc;
   __syncthreads();
   for (int s = 256; s > 0; s >>= 1) {
-    if (t < s) red[t] += red[t + s];
+    if (t < s) st[t] += st[t + s];
     __syncthreads();
   }
-  if (t == 0) part[blockIdx.x] = red[0];
+  if (t == 0) part[static_cast<long>(blockIdx.y) * gridDim.x + blockIdx.x] = st[0];
 }
 
-// out[0] = sum of part[0..n) in a fixed order (one block)
+// out[b] = sum of part[b n .. b n + n) in a fixed order, b = blockIdx.x
 __global__ __launch_bounds__(256) void sum_parts(const double* __restrict__ part, long n, double* out) {
   __shared__ double red[256];
+  part += blockIdx.x * n;
   double acc = 0.0;
   for (long x = threadIdx.x; x < n; x += 256) acc += part[x];
   red[threadIdx.x] = acc;
@@ -163,36 +187,7 @@ __global__ __launch_bounds__(256) void sum_parts(const double* __restrict__ part
     if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0];
-}
-
-// The distinct orderings of (i, j, k) and their read tiles.
-Orders orders_of(int i, int j, int k) {
-  Orders out{};
-  const int x[3] = {i, j, k};
-  std::vector<std::vector<int>> seen;
-  for (int p = 0; p < 6; ++p) {
-    const int e0 = perm_at(p, 0), e1 = perm_at(p, 1), e2 = perm_at(p, 2);
-    std::vector<int> key = {x[e0], x[e1], x[e2]};
-    bool dup = false;
-    for (auto& s : seen) dup = dup || s == key;
-    if (dup) continue;
-    seen.push_back(key);
-    // (i', j', k') = (x[pi(0)], x[pi(1)], x[pi(2)]); inv = pi^{-1}
-    int inv[3];
-    inv[e0] = 0;
-    inv[e1] = 1;
-    inv[e2] = 2;
-    Order& r = out.t[out.n++];
-    r.ip = key[0];
-    r.jp = key[1];
-    r.kp = key[2];
-    r.r1 = perm_index(inv[0], inv[1]);
-    r.r2 = perm_index((inv[0] + 1) % 3, (inv[1] + 1) % 3);
-    r.r3 = perm_index((inv[0] + 2) % 3, (inv[1] + 2) % 3);
-    r.r4 = perm_index(2 - inv[0], 2 - inv[1]);
-  }
-  return out;
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
 }  // namespace trip
@@ -229,7 +224,6 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
     set_error("ri_ccsd_triples: v = %d is too large for the energy tiles", v);
     return RI_E_ARG;
   }
-  const long ntiles = static_cast<long>(nt) * nt * nt;        // assembly tiles (ordered)
   const long ntri = static_cast<long>(nt) * (nt + 1) * (nt + 2) / 6;  // energy tile triples
   const long ntrip = static_cast<long>(o) * (o + 1) * (o + 2) / 6;
   // Each term of P, X(p, q, r; x, y, z) = sum_d (yd|xp) t2[r][q][z][d] - sum_l (zr|ql) t2[p][l][x][y],
@@ -237,27 +231,56 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
   //   A[p][x][y][e] = (yd|xp) for e = d < v,  t2[p][l][x][y] for e = v + l,
   //   Bt[r][q][z][e] = t2[r][q][z][d] for e = d < v,  -(zr|ql) for e = v + l.
   // Buffers: A [o][v][v][v+o], Bt [o][o][v][v+o], J [o][o][v][o], K [o][v][o][v],
-  // Y [6][v][v][v] (the six terms), W and V [v][v][v], tile partials, triplet sums.
+  // Y [batch][3][v][v][v] (the pair sums), tile partials, triplet sums, the GEMMs' offsets,
+  // the triplets, the tile triples.
+  // Batch: enough GEMM tiles (128 x 128) for four rounds of the chip's two workgroups per CU
+  // (one triplet at v = 120 is 339 tiles, 0.7 rounds), at most 16 triplets and 2 GiB of Y.
+  const long tiles = 3 * ((vv + 127) / 128) * ((v + 127) / 128);
+  long nb = std::min({(2048 + tiles - 1) / tiles, 16L, (1L << 28) / (3 * v3), ntrip});
+  nb = std::max(1L, nb);
   const size_t nA = static_cast<size_t>(o) * vv * vo, nBt = static_cast<size_t>(o) * o * v * vo,
                nJ = static_cast<size_t>(o) * o * v * o, nK = static_cast<size_t>(o) * v * o * v;
-  const size_t total = nA + nBt + nJ + nK + 8 * static_cast<size_t>(v3) + ntri + ntrip + (ntri + 1) / 2;
+  auto even = [](size_t x) { return (x + 1) / 2 * 2; };
+  const size_t bytes = (even(nA) + even(nBt) + even(nJ) + even(nK) + even(3 * nb * static_cast<size_t>(v3)) +
+                        nb * ntri + ntrip + 15 * static_cast<size_t>(ntrip)) * sizeof(double) +
+                       ntrip * sizeof(trip::Trip) + ntri * sizeof(int);
   void* buf = nullptr;
-  RI_TRY(dev_alloc(&buf, total * sizeof(double), s));
+  RI_TRY(dev_alloc(&buf, bytes, s));
   double* A = static_cast<double*>(buf);
-  double* Bt = A + nA;
-  double* J = Bt + nBt;
-  double* K = J + nJ;
-  double* Y = K + nK;
-  double* W = Y + 6 * v3;
-  double* Vt = W + v3;
-  double* part = Vt + v3;
-  double* et = part + ntri;
-  int* tl = reinterpret_cast<int*>(et + ntrip);
+  double* Bt = A + even(nA);
+  double* J = Bt + even(nBt);
+  double* K = J + even(nJ);
+  double* Y = K + even(nK);
+  double* part = Y + even(3 * nb * static_cast<size_t>(v3));
+  double* et = part + nb * ntri;
+  long* items = reinterpret_cast<long*>(et + ntrip);
+  trip::Trip* tp = reinterpret_cast<trip::Trip*>(items + 15 * ntrip);
+  int* tl = reinterpret_cast<int*>(tp + ntrip);
   std::vector<int> tiles_host;
   tiles_host.reserve(ntri);
   for (int ta = 0; ta < nt; ++ta)
     for (int tb = ta; tb < nt; ++tb)
       for (int tc = tb; tc < nt; ++tc) tiles_host.push_back(ta | (tb << 10) | (tc << 20));
+  // the triplets in order and, per triplet and pair, the offsets of its GEMM: (p, q, r) = the
+  // triplet and (x, y, z) = (a, b, c), both permuted by the pair's m; Y_m [x][y][z]
+  std::vector<trip::Trip> trips;
+  std::vector<long> items_host;
+  trips.reserve(ntrip);
+  items_host.reserve(15 * ntrip);
+  const long sA0 = vv * vo, sB1 = static_cast<long>(v) * vo;
+  for (int i = 0; i < o; ++i)
+    for (int j = i; j < o; ++j)
+      for (int k = j; k < o; ++k) {
+        const int x3[3] = {i, j, k};
+        for (int h = 0; h < 3; ++h) {
+          const int m = trip::term(h);
+          const long pp = x3[trip::perm_at(m, 0)], qq = x3[trip::perm_at(m, 1)], rr = x3[trip::perm_at(m, 2)];
+          const long at[5] = {pp * sA0, (rr * o + qq) * sB1, qq * sA0, (rr * o + pp) * sB1,
+                              (static_cast<long>(trips.size()) % nb * 3 + h) * v3};
+          items_host.insert(items_host.end(), at, at + 5);
+        }
+        trips.push_back(trip::Trip{i, j, k});
+      }
   int rc = RI_OK;
   {
     GemmArena arena;
@@ -268,14 +291,20 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
     const Tensor Bvo(B + static_cast<long>(o) * n, {Q, v, o}, {nn, n, 1});
     const Tensor Boo(B, {Q, o, o}, {nn, n, 1});
     const Tensor Bov(B + o, {Q, o, v}, {nn, n, 1});
-    const long sA2 = vo, sA1 = static_cast<long>(v) * vo, sA0 = vv * vo;  // strides of A
-    const long sB2 = vo, sB1 = static_cast<long>(v) * vo, sB0 = static_cast<long>(o) * v * vo;  // of Bt
+    const long sA2 = vo, sA1 = static_cast<long>(v) * vo;                    // strides of A
+    const long sB2 = vo, sB0 = static_cast<long>(o) * v * vo;  // of Bt
     do {
       if ((rc = check_hip(hipMemcpyAsync(tl, tiles_host.data(), ntri * sizeof(int), hipMemcpyHostToDevice, s),
                           "triples tiles")))
         break;
+      if ((rc = check_hip(hipMemcpyAsync(tp, trips.data(), ntrip * sizeof(trip::Trip), hipMemcpyHostToDevice, s),
+                          "triples list")))
+        break;
+      if ((rc = check_hip(hipMemcpyAsync(items, items_host.data(), 15 * ntrip * sizeof(long), hipMemcpyHostToDevice, s),
+                          "triples offsets")))
+        break;
       // zero padding of the summed index (columns v + o .. vo - 1)
-      if ((rc = check_hip(hipMemsetAsync(A, 0, (nA + nBt) * sizeof(double), s), "triples clear"))) break;
+      if ((rc = check_hip(hipMemsetAsync(A, 0, (even(nA) + even(nBt)) * sizeof(double), s), "triples clear"))) break;
       // A[p][x][y][d] = (yd|xp)
       if ((rc = einsum("Qyd,Qxp->pxyd", 1.0, Bvv, Bvo, 0.0, Tensor(A, {o, v, v, v}, {sA0, sA1, sA2, 1}), arena,
                        s)))
@@ -294,33 +323,51 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
         break;
       // K[i][a][j][b] = (ia|jb)
       if ((rc = einsum("Qia,Qjb->iajb", 1.0, Bov, Bov, 0.0, Tensor(K, {o, v, o, v}), arena, s))) break;
-      long tix = 0;
-      for (int i = 0; i < o && rc == RI_OK; ++i)
-        for (int j = i; j < o && rc == RI_OK; ++j)
-          for (int k = j; k < o && rc == RI_OK; ++k, ++tix) {
-            // term of permutation m: (p, q, r) = the triplet and (x, y, z) = (a, b, c), both
-            // permuted by m; its natural layout Y_m[x][y][z]
-            const int x3[3] = {i, j, k};
-            for (int m = 0; m < 6 && rc == RI_OK; ++m) {
-              const int pp = x3[trip::perm_at(m, 0)], qq = x3[trip::perm_at(m, 1)], rr = x3[trip::perm_at(m, 2)];
-              rc = einsum("xye,ze->xyz", 1.0, Tensor(A + pp * sA0, {v, v, vo}, {sA1, sA2, 1}),
-                          Tensor(Bt + (static_cast<long>(rr) * o + qq) * sB1, {v, vo}, {sB2, 1}), 0.0,
-                          Tensor(Y + m * v3, {v, v, v}), arena, s, precision);
-            }
+      // Y_m[x][y][z] = sum_e A[p][x][y][e] Bt[r][q][z][e] + A[q][y][x][e] Bt[r][p][z][e]
+      gemm::GemmDesc g{};
+      g.M = vv;
+      g.N = v;
+      g.K = vo;
+      g.M2 = v;
+      g.N2 = v;
+      g.K2 = 1;
+      g.K3 = vo;
+      g.a = A;
+      g.am1 = sA1;
+      g.am2 = sA2;
+      g.ak3 = 1;
+      g.b = Bt;
+      g.bn2 = vo;
+      g.bk3 = 1;
+      g.c = Y;
+      g.cm1 = vv;
+      g.cm2 = v;
+      g.cn2 = 1;
+      g.alpha = 1.0;
+      g.beta = 0.0;
+      for (long t0 = 0; t0 < ntrip && rc == RI_OK; t0 += nb) {
+        const long n_t = std::min(nb, ntrip - t0);
+        if (precision == RI_PREC_FP64) {
+          ProfScope ps(s, "xye,ze->xyz", 12.0 * n_t * static_cast<double>(v3) * vo);
+          rc = gemm::run_pairs(g, static_cast<int>(3 * n_t), items + 15 * t0, s);
+        } else {
+          for (long x = 0; x < 3 * n_t && rc == RI_OK; ++x) {
+            const long* at = &items_host[15 * t0 + 5 * x];
+            const Tensor Yt(Y + at[4], {v, v, v});
+            rc = einsum("xye,ze->xyz", 1.0, Tensor(A + at[0], {v, v, vo}, {sA1, sA2, 1}),
+                        Tensor(Bt + at[1], {v, vo}, {sB2, 1}), 0.0, Yt, arena, s, precision);
             if (rc) break;
-            {
-              ProfScope ps(s, "triples_assemble", 0.0, 8.0 * 8.0 * v3);
-              trip::assemble_wv<<<static_cast<unsigned>(ntiles), 512, 0, s>>>(Y, K, t1, o, v, i, j, k, W, Vt);
-              if ((rc = check_launch("triples_assemble"))) break;
-            }
-            {
-              ProfScope ps(s, "triples_energy", 0.0, 16.0 * v3);
-              const trip::Orders ord = trip::orders_of(i, j, k);
-              trip::energy_tiles<<<static_cast<unsigned>(ntri), 512, 0, s>>>(W, Vt, sys->eps, o, v, ord, tl, part);
-              trip::sum_parts<<<1, 256, 0, s>>>(part, ntri, et + tix);
-              if ((rc = check_launch("triples_energy"))) break;
-            }
+            rc = einsum("xye,ze->xyz", 1.0, Tensor(A + at[2], {v, v, vo}, {sA2, sA1, 1}),
+                        Tensor(Bt + at[3], {v, vo}, {sB2, 1}), 1.0, Yt, arena, s, precision);
           }
+        }
+        if (rc) break;
+        ProfScope ps(s, "triples_energy", 0.0, 24.0 * n_t * v3);
+        trip::energy_tiles<<<dim3(static_cast<unsigned>(ntri), static_cast<unsigned>(n_t)), 512, 0, s>>>(
+            Y, K, t1, sys->eps, o, v, tp + t0, tl, part);
+        trip::sum_parts<<<static_cast<unsigned>(n_t), 256, 0, s>>>(part, ntri, et + t0);
+        rc = check_launch("triples_energy");
+      }
       if (rc) break;
       std::vector<double> h(ntrip);
       if ((rc = check_hip(hipMemcpyAsync(h.data(), et, ntrip * sizeof(double), hipMemcpyDeviceToHost, s),
