@@ -472,6 +472,168 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void i
   }
 }
 
+// The same for hidden widths 64 NQ (NT = 4 NQ output tiles), with the activations kept in
+// registers.  The products are taken transposed, outputs by rows: the weights are the
+// first MFMA operand, and tile u of a layer holds outputs NT l + u (l = 0..15), so lane l
+// reads NT consecutive weights of a row as they lie in memory.  A lane's result element
+// (u, r) in lane group g = lane / 16 is output NT (4g + r) + u of row lane % 16; the next
+// layer's step s takes k = 4s + kq from lane group kq, so every four registers (u = 4a ..
+// 4a + 3, one r) are transposed against the four lane groups (two permlane32 and two
+// permlane16 swaps): register g of the quad then holds k = NT (4g + r) + 4a + kq.  k is
+// summed in the order of infer_kernel, so y is the same bit for bit.
+// Bound by the FP32 matrix pipe and the tanh; only the weights pass through LDS, rows of 16 k
+// (WR) loaded straight from memory two chunks ahead into a ring of three, shared by the four
+// waves (64 rows), two workgroups per CU, so that one workgroup's tanh runs under the
+// other's products.  At hidden 256, two layers, 42.5e6 rows 66.9 ms (91.3 ms with the
+// activations in LDS and the weights staged through registers, two barriers per 8 k); at
+// hidden 64, 128, 192 and 4.2e6 rows 1.05, 2.44, 4.35 ms (1.44, 3.34, 6.20 ms).
+// d_in a multiple of 4.  grid ceil(n / 64), block 256.
+constexpr int WR = 16;
+// x_q in lane group g -> x_g in lane group q.  (The swap builtins return both registers, but
+// the compiler dropped the second one here; the waits are those between a vector write and a
+// lane swap that reads it.)
+__device__ __forceinline__ void transpose_groups(float& x0, float& x1, float& x2, float& x3) {
+  asm("s_nop 1\n\t"
+      "v_permlane32_swap_b32 %0, %2\n\t"
+      "v_permlane32_swap_b32 %1, %3\n\t"
+      "s_nop 1\n\t"
+      "v_permlane16_swap_b32 %0, %1\n\t"
+      "v_permlane16_swap_b32 %2, %3\n\t"
+      "s_nop 1"
+      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
+}
+template <int NQ>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void infer_regs_kernel(
+    const float* __restrict__ X, long n, int d_in, int layers, const float* __restrict__ params,
+    float* __restrict__ y) {
+  constexpr int NT = 4 * NQ, HID = 16 * NT;
+  __shared__ float sW[3][WR * HID];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(w);
+  const int l16 = lane & 15, kq = lane >> 4;
+  const long row = static_cast<long>(blockIdx.x) * 64 + 16 * w + l16, rowc = row < n ? row : n - 1;
+  // the 16-byte pieces of a lane's weights: piece q of lane l at NQ l + (q ^ sw(l)), which
+  // spreads the sixteen lanes of one read over the banks
+  auto sw = [](int l) { return NQ == 4 ? (l >> 2) & 3 : 0; };
+
+  // chunks of WR weight rows in the order of use: those of the first layer, then HID / WR for
+  // every further hidden layer; loads run two chunks ahead of the products
+  const int nch1 = (d_in + WR - 1) / WR;
+  const float* lw = params;  // weights of the layer being loaded
+  int lrow = 0, lfin = d_in, lleft = layers, lslot = 0;
+  auto load_chunk = [&] {
+    if (lleft == 0) {  // past the last chunk: any valid rows, to keep the count of loads
+      lw = params;
+      lrow = 0;
+      lfin = d_in;
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int p = t + 256 * i, k = p / (4 * NT), pos = p % (4 * NT), l = pos / NQ, q = (pos % NQ) ^ sw(l);
+      const int kr = lrow + k < lfin ? lrow + k : lfin - 1;
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(lw + static_cast<size_t>(kr) * HID + 4 * (NQ * l + q)),
+          (__attribute__((address_space(3))) void*)(&sW[0][0] + lslot * (WR * HID) + 4 * (wv * 64 + 256 * i)), 16, 0, 0);
+    }
+    lslot = lslot == 2 ? 0 : lslot + 1;
+    lrow += WR;
+    if (lleft > 0 && lrow >= lfin) {
+      lw += static_cast<size_t>(lfin) * HID + HID;
+      lrow = 0;
+      lfin = HID;
+      --lleft;
+    }
+  };
+  int slot = 0;  // of the chunk being used
+  auto next_chunk = [&] {
+    // its loads have landed in every wave and the slot before it is free
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NQ) : "memory");
+    load_chunk();
+  };
+  auto done_chunk = [&] { slot = slot == 2 ? 0 : slot + 1; };
+  f32x4_t acc[NT], wf[2][NQ];
+  auto wread = [&](int p, int s4) {  // weights of k = s4 .. s4 + 3 of the chunk
+    const float* base = &sW[0][0] + slot * (WR * HID) + (s4 + kq) * HID;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) wf[p][q] = *reinterpret_cast<const f32x4_t*>(base + 4 * (NQ * l16 + (q ^ sw(l16))));
+  };
+  auto step = [&](int p, float x) {
+#pragma unroll
+    for (int u = 0; u < NT; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[p][u >> 2][u & 3], x, acc[u], 0, 0, 0);
+  };
+  float h[NT][4];  // activations: [4a + g][r] after the transposition
+  auto activate = [&](const float* b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int a = 0; a < NQ; ++a) {
+        const f32x4_t bias = {b[NT * (4 * kq + r) + 4 * a], b[NT * (4 * kq + r) + 4 * a + 1],
+                              b[NT * (4 * kq + r) + 4 * a + 2], b[NT * (4 * kq + r) + 4 * a + 3]};
+        float x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float val = 1.f * acc[4 * a + q][r];
+          val += bias[q];
+          x[q] = tanhf(val);
+        }
+        transpose_groups(x[0], x[1], x[2], x[3]);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) h[4 * a + g][r] = x[g];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) acc[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+#pragma unroll
+  for (int u = 0; u < NT; ++u) acc[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  load_chunk();
+  load_chunk();
+  // first layer: the inputs straight from memory
+  for (int ch = 0; ch < nch1; ++ch) {
+    next_chunk();
+    for (int s4 = 0; s4 < WR && ch * WR + s4 < d_in; s4 += 4) {
+      wread(0, s4);
+      step(0, X[rowc * d_in + ch * WR + s4 + kq]);
+    }
+    done_chunk();
+  }
+  const float* Wl = params + static_cast<size_t>(d_in) * HID;  // biases of the layer just done
+  activate(Wl);
+  Wl += HID;
+  for (int l = 1; l < layers; ++l) {
+#pragma unroll
+    for (int ch = 0; ch < HID / WR; ++ch) {
+      next_chunk();
+      wread(0, 0);
+#pragma unroll
+      for (int i = 0; i < WR / 4; ++i) {
+        if (i + 1 < WR / 4) wread((i + 1) & 1, 4 * (i + 1));
+        const int s = ch * (WR / 4) + i, m = s / NQ, a = s % NQ;  // k = 4s + kq = NT m + 4a + kq
+        step(i & 1, h[4 * a + (m >> 2)][m & 3]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      done_chunk();
+    }
+    Wl += static_cast<size_t>(HID) * HID;
+    activate(Wl);
+    Wl += HID;
+  }
+  // output layer: one row of weights in the first operand
+  f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < HID / 4; ++s) {
+    const int m = s / NQ, a = s % NQ;
+    const float wo = l16 == 0 ? Wl[4 * s + kq] : 0.f;
+    o = __builtin_amdgcn_mfma_f32_16x16x4f32(wo, h[4 * a + (m >> 2)][m & 3], o, 0, 0, 0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load is left to land in LDS
+  if (kq == 0 && row < n) {
+    float val = 1.f * o[0];
+    val += Wl[HID];
+    y[row] = val;
+  }
+}
+
 inline unsigned nblk(long n) { return static_cast<unsigned>((n + 255) / 256); }
 
 inline bool infer_ok(const ri_mlp* net) {
@@ -480,10 +642,15 @@ inline bool infer_ok(const ri_mlp* net) {
 
 template <int NT>
 static void launch_infer(const ri_mlp* net, const float* X, long n, float* y, hipStream_t s) {
-  infer_kernel<NT><<<static_cast<unsigned>((n + IR - 1) / IR), 256, 0, s>>>(X, n, net->d_in, net->layers,
-                                                                           net->params, y);
+  const unsigned grid = static_cast<unsigned>((n + IR - 1) / IR);
+  if constexpr (NT % 4 == 0)
+    infer_regs_kernel<NT / 4><<<grid, 256, 0, s>>>(X, n, net->d_in, net->layers, net->params, y);
+  else
+    infer_kernel<NT><<<grid, 256, 0, s>>>(X, n, net->d_in, net->layers, net->params, y);
 }
-// y = net(X), n rows, by infer_kernel (chunks of 2^24 workgroups at most)
+// y = net(X), n rows, without keeping activations (chunks of 2^24 workgroups at most): in
+// registers for hidden widths of whole quads of tiles (faster at every such width and row
+// count, see infer_regs_kernel), through LDS for the others
 int infer(const ri_mlp* net, const float* X, long n, float* y, hipStream_t s) {
   const long step = static_cast<long>(IR) << 24;
   for (long r0 = 0; r0 < n; r0 += step) {
