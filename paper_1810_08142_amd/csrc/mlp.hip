@@ -27,6 +27,7 @@ struct ri_mlp {
   float y_scale = 1.f;
   float* scratch = nullptr;  // activations and deltas for up to `rows` rows
   long rows = 0;
+  int deltas = 0;            // delta buffers in it
   size_t scratch_bytes = 0;
 };
 
@@ -634,6 +635,439 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
+// ---------------------------------------------------------------- gradient kernels
+// Loss and gradient for hidden widths 64 NQ in three launches.  A batch of 4096 rows has
+// 1.6 GFLOP (11 us of the FP32 matrix pipe), so what counts is the number of dependent
+// launches and that every CU has work in each: layer by layer (one GEMM per product, tanh',
+// and two column-sum stages per layer) it took 21 launches of 2-46 us, 341 us with the loss
+// read back; now step 28, weight gradients 6.4, sums 2.4 us, 70 us in all.
+//
+// step_kernel: forward, loss and backward of 16 RT rows per workgroup, everything between
+// the layers in LDS; H (activations) and D (deltas) also go to memory for the weight
+// gradients.  The four waves share the outputs of a layer (tile u of wave w: outputs
+// 16 NQ w + NQ j + u, j = 0..15), so each weight is read by one wave only and goes from L2
+// straight to the MFMA operand; the loads run two chunks ahead of the products.  Products
+// are transposed (weights first): a lane ends with 4 NQ consecutive outputs of row l16,
+// m0 + NQ r + u.  k is permuted alike in both operands (lane group kq takes 4 or 8
+// consecutive k), which makes the LDS and the backward weight reads 16 bytes wide.
+// RT = 2 halves the weight traffic per row and is taken where every CU still gets a
+// workgroup.  Alone on a CU a workgroup of 16 rows takes 20 us: 7 us of MFMAs, the rest the
+// tanh and the chain load - product - barrier of the layers; two workgroups per CU overlap
+// those (65536 rows: 232 us, MFMAs 109 us).
+// Sums over the rows that are no products (biases, output layer, loss) are kept per
+// workgroup in cs [workgroup][CSW]: layers x HID bias sums, HID output weights, the output
+// bias, the squared error; rows past n count with a zero residual.
+constexpr int STEP_WGS = 2048;  // workgroups at most; each loops over its row tiles
+struct StepArgs {
+  const float *X, *Y, *params;
+  long n, lstride;  // rows; elements between the layers of H and D
+  int d_in, layers;
+  float *H, *D, *cs;
+};
+inline __host__ __device__ int cs_width(int hidden, int layers) { return (layers + 1) * hidden + 4; }
+
+template <int N>
+struct vecf {
+  float v[N];
+};
+template <int N>
+__device__ __forceinline__ vecf<N> ldv(const float* p) {
+  vecf<N> r;
+  if constexpr (N == 4) {
+    const f32x4_t x = *reinterpret_cast<const f32x4_t*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = x[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) r.v[i] = p[i];
+  }
+  return r;
+}
+
+template <int NQ, int RT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void step_kernel(StepArgs g) {
+  constexpr int HID = 64 * NQ, R = 16 * RT, LS = HID + 4, NCH = HID / 16;
+  constexpr int FB = 3, BB = 2;  // weight chunks held, forward and backward
+  __shared__ __align__(16) float sh[2][R * LS];
+  __shared__ float sdot[4][R], sdy[R];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
+  const int m0 = 16 * NQ * w + 4 * NQ * kq;   // the lane's first output
+  const int wc = 16 * NQ * w + NQ * l16;      // the outputs whose weights it loads: wc + u
+  const int L = g.layers, d_in = g.d_in, kx = (d_in + 15) & ~15;
+  const float* const W1 = g.params + static_cast<size_t>(d_in) * HID + HID;  // second layer on
+  constexpr size_t WL = static_cast<size_t>(HID) * HID + HID;
+  float* const cs = g.cs + static_cast<size_t>(blockIdx.x) * cs_width(HID, L);
+  bool first = true;
+
+  f32x4_t acc[RT][NQ];
+  vecf<NQ> wf[FB][4];  // forward weights, chunks of 16 k
+  auto fload = [&](const float* W, int ch) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) wf[ch % FB][e] = ldv<NQ>(W + static_cast<size_t>(16 * ch + 4 * kq + e) * HID + wc);
+  };
+  auto zero = [&] {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int u = 0; u < NQ; ++u) acc[rt][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  // the lane's values of acc to LDS buffer b and to the layer's rows in memory
+  auto store = [&](int b, float* G, long row0) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      float* ls = &sh[b][(16 * rt + l16) * LS + m0];
+      float* gs = G + (row0 + 16 * rt + l16) * HID + m0;
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        f32x4_t x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = acc[rt][(4 * i + e) % NQ][(4 * i + e) / NQ];
+        *reinterpret_cast<f32x4_t*>(ls + 4 * i) = x;
+        *reinterpret_cast<f32x4_t*>(gs + 4 * i) = x;
+      }
+    }
+  };
+  f32x4_t bv[NQ];  // the biases of the lane's outputs, read before a layer's products
+  auto bias = [&](const float* b) {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) bv[i] = *reinterpret_cast<const f32x4_t*>(b + m0 + 4 * i);
+  };
+  auto activate = [&] {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4 * NQ; ++i)
+        acc[rt][i % NQ][i / NQ] = tanhf(acc[rt][i % NQ][i / NQ] + bv[i / 4][i % 4]);
+  };
+  auto put = [&](int c, float x) { cs[c] = first ? x : cs[c] + x; };
+  // column sums of LDS buffer b into cs[c0 ..]
+  auto colsum = [&](int b, int c0) {
+    if (t < HID) {
+      float x = 0.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) x += sh[b][r * LS + t];
+      put(c0 + t, x);
+    }
+  };
+
+  for (long row0 = static_cast<long>(blockIdx.x) * R; row0 < g.n; row0 += static_cast<long>(gridDim.x) * R) {
+    if (!first) __syncthreads();
+    int cur = 0;
+    auto iload = [&](int k) { return ldv<NQ>(g.params + static_cast<size_t>(k < d_in ? k : 0) * HID + wc); };
+    vecf<NQ> wi[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) wi[e] = iload(4 * kq + e);
+    bias(W1 - HID);
+    for (int p = t; p < R * kx; p += 256) {
+      const int r = p / kx, k = p - r * kx;
+      const long row = std::min(row0 + r, g.n - 1);
+      sh[0][r * LS + k] = k < d_in ? g.X[row * d_in + k] : 0.f;
+    }
+    __syncthreads();
+    if (L > 1) {
+#pragma unroll
+      for (int ch = 0; ch < FB - 1 && ch < NCH; ++ch) fload(W1, ch);
+    }
+    zero();
+    for (int k0 = 0; k0 < kx; k0 += 16) {
+      f32x4_t x[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) x[rt] = *reinterpret_cast<const f32x4_t*>(&sh[0][(16 * rt + l16) * LS + k0 + 4 * kq]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * kq + e;
+#pragma unroll
+        for (int u = 0; u < NQ; ++u)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[rt][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(k < d_in ? wi[e].v[u] : 0.f, x[rt][e], acc[rt][u], 0, 0, 0);
+        if (k0 + 16 < kx) wi[e] = iload(k + 16);
+      }
+    }
+    const float* W = W1;
+    activate();
+    store(1, g.H, row0);
+    cur = 1;
+    __syncthreads();
+    for (int l = 1; l < L; ++l) {
+      zero();
+      bias(W + static_cast<size_t>(HID) * HID);
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        if (ch + FB - 1 < NCH) fload(W, ch + FB - 1);
+        f32x4_t x[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          x[rt] = *reinterpret_cast<const f32x4_t*>(&sh[cur][(16 * rt + l16) * LS + 16 * ch + 4 * kq]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int u = 0; u < NQ; ++u)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              acc[rt][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[ch % FB][e].v[u], x[rt][e], acc[rt][u], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      W += WL;
+      if (l + 1 < L) {
+#pragma unroll
+        for (int ch = 0; ch < FB - 1 && ch < NCH; ++ch) fload(W, ch);
+      }
+      activate();
+      cur ^= 1;
+      store(cur, g.H + l * g.lstride, row0);
+      __syncthreads();
+    }
+    // output layer: W is its weight column, W[HID] its bias
+    float dot[RT];
+    f32x4_t wo[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) wo[i] = *reinterpret_cast<const f32x4_t*>(W + m0 + 4 * i);
+    const float bo = W[HID], yt = g.Y[std::min(row0 + (lane & (R - 1)), g.n - 1)];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      dot[rt] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4 * NQ; ++i) dot[rt] += acc[rt][i % NQ][i / NQ] * wo[i / 4][i % 4];
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      dot[rt] += __shfl_xor(dot[rt], 16);
+      dot[rt] += __shfl_xor(dot[rt], 32);
+      if (kq == 0) sdot[w][16 * rt + l16] = dot[rt];
+    }
+    __syncthreads();
+    if (w == 0) {
+      float res = 0.f;
+      if (lane < R && row0 + lane < g.n)
+        res = sdot[0][lane] + sdot[1][lane] + (sdot[2][lane] + sdot[3][lane]) + bo - yt;
+      float dy = 2.f * res / static_cast<float>(g.n), sq = res * res;
+      if (lane < R) sdy[lane] = dy;
+#pragma unroll
+      for (int x = 1; x < R; x <<= 1) {
+        dy += __shfl_xor(dy, x);
+        sq += __shfl_xor(sq, x);
+      }
+      if (lane == 0) {
+        put((L + 1) * HID, dy);
+        put((L + 1) * HID + 1, sq);
+      }
+    }
+    __syncthreads();
+    if (t < HID) {  // output weights
+      float x = 0.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) x += sh[cur][r * LS + t] * sdy[r];
+      put(L * HID + t, x);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const float dy = sdy[16 * rt + l16];
+#pragma unroll
+      for (int i = 0; i < 4 * NQ; ++i) {
+        const float h = acc[rt][i % NQ][i / NQ];
+        acc[rt][i % NQ][i / NQ] = dy * wo[i / 4][i % 4] * (1.f - h * h);
+      }
+    }
+    cur ^= 1;
+    store(cur, g.D + (L - 1) * g.lstride, row0);
+    __syncthreads();
+    colsum(cur, (L - 1) * HID);
+    for (int l = L - 1; l >= 1; --l) {
+      // delta of layer l - 1: sum_k delta(row, k) W(m, k); chunks of 32 k, a lane group 8
+      W -= WL;
+      zero();
+      vecf<4> wb[BB][NQ][2];
+      auto bload = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) wb[c % BB][u][i] = ldv<4>(W + static_cast<size_t>(wc + u) * HID + 32 * c + 8 * kq + 4 * i);
+      };
+#pragma unroll
+      for (int c = 0; c < BB - 1 && c < HID / 32; ++c) bload(c);
+      f32x4_t hv[RT][NQ];  // this thread's own stores of the forward pass
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+          hv[rt][i] = *reinterpret_cast<const f32x4_t*>(g.H + (l - 1) * g.lstride + (row0 + 16 * rt + l16) * HID + m0 + 4 * i);
+#pragma unroll
+      for (int c = 0; c < HID / 32; ++c) {
+        if (c + BB - 1 < HID / 32) bload(c + BB - 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          f32x4_t x[RT];
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            x[rt] = *reinterpret_cast<const f32x4_t*>(&sh[cur][(16 * rt + l16) * LS + 32 * c + 8 * kq + 4 * i]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int u = 0; u < NQ; ++u)
+#pragma unroll
+              for (int rt = 0; rt < RT; ++rt)
+                acc[rt][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[c % BB][u][i].v[e], x[rt][e], acc[rt][u], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4 * NQ; ++i) {
+          const float h = hv[rt][i / 4][i % 4];
+          acc[rt][i % NQ][i / NQ] *= 1.f - h * h;
+        }
+      cur ^= 1;
+      store(cur, g.D + (l - 1) * g.lstride, row0);
+      __syncthreads();
+      colsum(cur, (l - 1) * HID);
+    }
+    first = false;
+  }
+}
+
+// Weight gradients W_l = H_{l-1}^T D_l of all hidden layers, partial sums over a range of
+// kper rows: part[split] in the order of the parameters.  A workgroup takes a 64 x 64 tile
+// of a hidden layer, or 16 x 64 of the first (few inputs), and its four waves a quarter of
+// the rows each, with the whole tile in their accumulators: both operands lie along the
+// outputs in memory, so a lane reads four of them (tile u, v: outputs 4 l16 + u, v) and
+// sixteen MFMAs follow two 16-byte loads, straight from memory.  The waves' sums are added
+// through LDS.  Rows past n have D = 0.
+// grid ((layers - 1) NQ^2 + ceil(d_in / 16) NQ, splits)
+struct WgradArgs {
+  const float *X, *H, *D;
+  long n, lstride, kper, pstride;
+  int d_in, layers;
+  float* part;
+};
+template <int NQ, int MT>
+__device__ __forceinline__ void wgrad_tile(const float* A, long lda, int m0, int M, long nA, const float* B, int n0,
+                                           long lo, long hi, float* out, float* red) {
+  constexpr int HID = 64 * NQ;
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
+  f32x4_t acc[MT][4];
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[u][v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // the wave's rows: a quarter of the range in blocks of 16
+  const long blocks = hi > lo ? (hi - lo) / 16 : 0, b0 = blocks * w / 4, b1 = blocks * (w + 1) / 4;
+  vecf<MT> a[2][4];
+  vecf<4> b[2][4];
+  const bool mok = MT == 4 || m0 + l16 < M;
+  auto load = [&](int p, long blk) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const long k = lo + 16 * blk + 4 * s + kq;
+      if constexpr (MT == 4)
+        a[p][s] = ldv<4>(A + k * lda + m0 + 4 * l16);
+      else
+        a[p][s].v[0] = mok ? A[std::min(k, nA - 1) * lda + m0 + l16] : 0.f;
+      b[p][s] = ldv<4>(B + k * HID + n0 + 4 * l16);
+    }
+  };
+  auto mul = [&](int p) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][s].v[u], b[p][s].v[v], acc[u][v], 0, 0, 0);
+  };
+  if (b0 < b1) load(0, b0);
+  for (long blk = b0; blk < b1; blk += 2) {
+    if (blk + 1 < b1) load(1, blk + 1);
+    mul(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (blk + 1 < b1) {
+      if (blk + 2 < b1) load(0, blk + 2);
+      mul(1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  f32x4_t* r4 = reinterpret_cast<f32x4_t*>(red);  // [wave][u][r][lane]
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      r4[((w * MT + u) * 4 + r) * 64 + lane] = f32x4_t{acc[u][0][r], acc[u][1][r], acc[u][2][r], acc[u][3][r]};
+  __syncthreads();
+  // wave w adds the rows r = w of every tile
+#pragma unroll
+  for (int u = 0; u < MT; ++u) {
+    f32x4_t x = r4[(u * 4 + w) * 64 + lane];
+#pragma unroll
+    for (int z = 1; z < 4; ++z) x += r4[((z * MT + u) * 4 + w) * 64 + lane];
+    const int m = m0 + MT * (4 * kq + w) + u;
+    if (m < M) *reinterpret_cast<f32x4_t*>(out + static_cast<size_t>(m) * HID + n0 + 4 * l16) = x;
+  }
+}
+template <int NQ>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void wgrad_kernel(WgradArgs g) {
+  constexpr int HID = 64 * NQ;
+  __shared__ __align__(16) float red[4 * 64 * 64];
+  const int nh = (g.layers - 1) * NQ * NQ;
+  const long np = (g.n + 15) & ~15L, lo = blockIdx.y * g.kper, hi = std::min(np, lo + g.kper);
+  float* part = g.part + blockIdx.y * g.pstride;
+  int b = blockIdx.x;
+  if (b < nh) {
+    const int l = 1 + b / (NQ * NQ), r = b % (NQ * NQ);
+    wgrad_tile<NQ, 4>(g.H + (l - 1) * g.lstride, HID, (r / NQ) * 64, HID, g.n, g.D + l * g.lstride, (r % NQ) * 64, lo,
+                      hi, part + static_cast<size_t>(g.d_in) * HID + HID + (l - 1) * (static_cast<size_t>(HID) * HID + HID),
+                      red);
+  } else {
+    b -= nh;
+    wgrad_tile<NQ, 1>(g.X, g.d_in, (b / NQ) * 16, g.d_in, g.n, g.D, (b % NQ) * 64, lo, hi, part, red);
+  }
+}
+
+// grad and loss from the partial sums, in a fixed order.  Blocks of the first kind take 256
+// weights each (all parameters up to the output layer; the biases among them are left to the
+// second kind), those of the second 32 columns of cs over the P workgroups of step_kernel.
+struct GsumArgs {
+  const float *part, *cs;
+  long pstride, nw;  // nw: parameters up to the output layer
+  int splits, P, hidden, layers, d_in;
+  long n;
+  float *grad, *loss;
+};
+__global__ __launch_bounds__(256) void gsum_kernel(GsumArgs g) {
+  __shared__ float sh[8][33];
+  const long w1 = static_cast<long>(g.d_in) * g.hidden, wl = static_cast<long>(g.hidden) * g.hidden;
+  const int nwb = static_cast<int>((g.nw + 255) / 256), t = threadIdx.x;
+  if (static_cast<int>(blockIdx.x) < nwb) {
+    const long i = blockIdx.x * 256L + t;
+    if (i >= g.nw) return;
+    const long j = i - w1 - g.hidden;  // past the first layer
+    if (j < 0 ? i >= w1 : j % (wl + g.hidden) >= wl) return;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int z = 0; z < g.splits; ++z) acc += g.part[z * g.pstride + i];
+    g.grad[i] = acc;
+    return;
+  }
+  const int ncs = (g.layers + 1) * g.hidden + 2, csw = cs_width(g.hidden, g.layers);
+  const int c = (blockIdx.x - nwb) * 32 + (t & 31), q = t >> 5;
+  float acc = 0.f;
+  if (c < ncs) {
+#pragma unroll 8
+    for (int p = q; p < g.P; p += 8) acc += g.cs[static_cast<long>(p) * csw + c];
+  }
+  sh[q][t & 31] = acc;
+  __syncthreads();
+  if (q || c >= ncs) return;
+  acc = ((sh[0][t] + sh[1][t]) + (sh[2][t] + sh[3][t])) + ((sh[4][t] + sh[5][t]) + (sh[6][t] + sh[7][t]));
+  const int l = c / g.hidden;
+  if (l < g.layers)
+    g.grad[w1 + l * (wl + g.hidden) + c % g.hidden] = acc;
+  else if (c < ncs - 1)
+    g.grad[g.nw + c - g.layers * g.hidden] = acc;
+  else
+    *g.loss = acc / static_cast<float>(g.n);
+}
+
 inline unsigned nblk(long n) { return static_cast<unsigned>((n + 255) / 256); }
 
 inline bool infer_ok(const ri_mlp* net) {
@@ -707,32 +1141,68 @@ inline void layer_ptrs(const ri_mlp* net, float* base, int k, float*& W, float*&
   }
 }
 
-// scratch layout for `rows` rows: H[1..layers] [rows][h], D (delta) [rows][h] x 2, y [rows],
-// dy [rows], split partials [SPLITS][h*h], loss partials [LB] + 1
+// gradient by step_kernel, wgrad_kernel and gsum_kernel: hidden widths of 64 to 256 in steps
+// of 64 and at most as many inputs
+inline bool step_ok(const ri_mlp* net) {
+  return net->hidden % 64 == 0 && net->hidden <= HMAX && net->d_in <= net->hidden;
+}
+constexpr int CUS = 256;  // compute units the splits are made for (the scratch layout follows them)
 constexpr int SPLITS = 32;
-int reserve(ri_mlp* net, long rows, hipStream_t s) {
-  if (rows <= net->rows) return RI_OK;
+// row ranges of wgrad_kernel: one 64 x 64 tile per CU, at least 64 rows in each
+inline int wgrad_splits(const ri_mlp* net, long n) {
+  const int nq = net->hidden / 64, tiles = std::max(1, (net->layers - 1) * nq * nq);
+  const long most = std::min<long>(SPLITS, (n + 63) / 64);
+  return static_cast<int>(std::max(1L, std::min<long>(most, CUS / tiles)));
+}
+
+// scratch layout for `rows` rows: H[1..layers] [rows][h], D (delta) [deltas][rows][h], y [rows],
+// dy [rows], split partials, column sums per workgroup, loss partials [LB] + 1
+struct ScrSize {
+  size_t part, cs;
+};
+inline ScrSize scr_size(const ri_mlp* net, long rows) {
+  const size_t h = net->hidden, d = net->d_in;
+  ScrSize z{SPLITS * std::max(std::max(h * h, h * d), h * 64), 0};
+  if (step_ok(net)) {
+    z.part = std::max(z.part, wgrad_splits(net, 1L << 24) * net->nparams);
+    z.cs = static_cast<size_t>(std::min<long>(STEP_WGS, (rows + 15) / 16)) * cs_width(net->hidden, net->layers);
+  }
+  z.part = round_up(z.part, 4);
+  return z;
+}
+int reserve(ri_mlp* net, long rows, int deltas, hipStream_t s) {
+  rows = round_up(rows, 32);  // whole row tiles
+  if (rows <= net->rows && deltas <= net->deltas) return RI_OK;
+  rows = std::max(rows, net->rows);
+  deltas = std::max(deltas, net->deltas);
   const size_t h = net->hidden;
   const size_t n = static_cast<size_t>(rows);
-  const size_t floats = net->layers * n * h + 2 * n * h + 2 * n + SPLITS * std::max(h * h, h * 64) + LB + 16;
+  const ScrSize z = scr_size(net, rows);
+  const size_t floats = net->layers * n * h + deltas * n * h + 2 * n + z.part + z.cs + LB + 16;
   if (net->scratch) dev_free(net->scratch, s);
   net->scratch = nullptr;
   net->rows = 0;
+  net->deltas = 0;
   void* p = nullptr;
   RI_TRY(dev_alloc(&p, floats * sizeof(float), s));
   net->scratch = static_cast<float*>(p);
   net->rows = rows;
+  net->deltas = deltas;
   net->scratch_bytes = floats * sizeof(float);
   return RI_OK;
 }
+// delta buffers that gradient() needs: one per layer where the weight gradients follow all
+// deltas, two in turn where each follows its own
+inline int grad_deltas(const ri_mlp* net) { return step_ok(net) ? std::max(2, net->layers) : 2; }
 
 struct Scr {
   std::vector<float*> H;  // H[1..layers]
-  float *D0, *D1, *y, *dy, *part, *lpart, *loss;
+  float *D0, *D1, *y, *dy, *part, *cs, *lpart, *loss;
 };
 Scr carve(const ri_mlp* net) {
   Scr c;
   const size_t h = net->hidden, n = static_cast<size_t>(net->rows);
+  const ScrSize z = scr_size(net, net->rows);
   float* p = net->scratch;
   c.H.push_back(nullptr);
   for (int l = 0; l < net->layers; ++l) {
@@ -740,15 +1210,16 @@ Scr carve(const ri_mlp* net) {
     p += n * h;
   }
   c.D0 = p;
-  p += n * h;
-  c.D1 = p;
-  p += n * h;
+  c.D1 = p + n * h;
+  p += net->deltas * n * h;
   c.y = p;
   p += n;
   c.dy = p;
   p += n;
   c.part = p;
-  p += SPLITS * std::max(h * h, h * 64);
+  p += z.part;
+  c.cs = p;
+  p += z.cs;
   c.lpart = p;
   p += LB;
   c.loss = p;
@@ -793,8 +1264,44 @@ int forward(ri_mlp* net, const float* X, long n, float* y, hipStream_t s) {
   return RI_OK;
 }
 
+template <int NQ>
+static int step_gradient(ri_mlp* net, const float* X, const float* Y, long n, float* grad, hipStream_t s) {
+  const Scr c = carve(net);
+  const long lstride = net->rows * net->hidden;
+  // 32 rows per workgroup where that still gives every CU a workgroup (128 workgroups of 32
+  // rows take longer for 4096 rows, 42 us, than 256 of 16 rows, 28 us)
+  const int R = n >= 32L * CUS ? 32 : 16;
+  const unsigned P = static_cast<unsigned>(std::min<long>(STEP_WGS, (n + R - 1) / R));
+  StepArgs sa{X, Y, net->params, n, lstride, net->d_in, net->layers, c.H[1], c.D0, c.cs};
+  if (R == 32)
+    step_kernel<NQ, 2><<<P, 256, 0, s>>>(sa);
+  else
+    step_kernel<NQ, 1><<<P, 256, 0, s>>>(sa);
+  RI_TRY(check_launch("step_kernel"));
+  const int splits = wgrad_splits(net, n);
+  const long kper = round_up((n + splits - 1) / splits, 64);
+  const unsigned tiles = (net->layers - 1) * NQ * NQ + (net->d_in + 15) / 16 * NQ;
+  const long pstride = static_cast<long>(net->nparams - net->hidden - 1);
+  WgradArgs wa{X, c.H[1], c.D0, n, lstride, kper, pstride, net->d_in, net->layers, c.part};
+  wgrad_kernel<NQ><<<dim3(tiles, splits), 256, 0, s>>>(wa);
+  RI_TRY(check_launch("wgrad_kernel"));
+  GsumArgs ga{c.part, c.cs, pstride, pstride, splits, static_cast<int>(P), net->hidden, net->layers, net->d_in, n, grad,
+              c.loss};
+  const unsigned blocks = nblk(pstride) + ((net->layers + 1) * net->hidden + 2 + 31) / 32;
+  gsum_kernel<<<blocks, 256, 0, s>>>(ga);
+  return check_launch("gsum_kernel");
+}
+
 // grad (device) and loss (device scalar in scratch) for the batch
 int gradient(ri_mlp* net, const float* X, const float* Y, long n, float* grad, hipStream_t s) {
+  if (step_ok(net)) {
+    switch (net->hidden / 64) {
+      case 1: return step_gradient<1>(net, X, Y, n, grad, s);
+      case 2: return step_gradient<2>(net, X, Y, n, grad, s);
+      case 3: return step_gradient<3>(net, X, Y, n, grad, s);
+      default: return step_gradient<4>(net, X, Y, n, grad, s);
+    }
+  }
   RI_TRY(forward(net, X, n, carve(net).y, s));
   Scr c = carve(net);
   mse_stage1<<<LB, 256, 0, s>>>(c.y, Y, n, c.dy, c.lpart);
@@ -1125,7 +1632,7 @@ int ri_mlp_forward(ri_mlp* net, const float* X, long n, float* y, void* stream) 
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const long chunk = 1L << 20;
-  RI_TRY(mlp::reserve(net, std::min(n, chunk), s));
+  RI_TRY(mlp::reserve(net, std::min(n, chunk), 2, s));
   for (long r0 = 0; r0 < n; r0 += chunk) {
     const long nn = std::min(chunk, n - r0);
     RI_TRY(mlp::forward(net, X + r0 * net->d_in, nn, y + r0, s));
@@ -1141,7 +1648,7 @@ int ri_mlp_gradient(ri_mlp* net, const float* X, const float* Y, long n, float* 
     return RI_E_ARG;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  RI_TRY(mlp::reserve(net, n, s));
+  RI_TRY(mlp::reserve(net, n, mlp::grad_deltas(net), s));
   float* g = grad ? grad : net->grad;
   RI_TRY(mlp::gradient(net, X, Y, n, g, s));
   if (loss_host) {
@@ -1159,7 +1666,7 @@ int ri_mlp_train_step(ri_mlp* net, const float* X, const float* Y, long n, float
     return RI_E_ARG;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  RI_TRY(mlp::reserve(net, n, s));
+  RI_TRY(mlp::reserve(net, n, mlp::grad_deltas(net), s));
   RI_TRY(mlp::gradient(net, X, Y, n, net->grad, s));
   RI_TRY(mlp::adam_step(net, lr, s));
   if (loss_host) {
@@ -1225,7 +1732,7 @@ int ri_mlp_train(ri_mlp* net, const float* X, const float* Y, long n, const floa
   const long steps = std::max(1L, n / o.batch);
   const long total = static_cast<long>(o.epochs) * steps;
   const long warm = std::max(1L, static_cast<long>(static_cast<double>(total) * static_cast<double>(o.warmup)));
-  RI_TRY(mlp::reserve(net, bs, s));
+  RI_TRY(mlp::reserve(net, bs, mlp::grad_deltas(net), s));
 
   // workspace: shuffled X [n][d] and Y [n], validation outputs [n_val], loss
   // histories [2][epochs], permutation [n]
@@ -1478,7 +1985,7 @@ int ri_mlp_guess(ri_mlp* net, const ri_system* sys, double* t1, double* t2, void
     nm.inv_std[k] = 1.f / net->stdv[k];
   }
   int rc = cc::mp2_with_integrals(sys, gov, t1, t2m, s);
-  if (rc == RI_OK && !fused) rc = mlp::reserve(net, chunk, s);
+  if (rc == RI_OK && !fused) rc = mlp::reserve(net, chunk, 2, s);
   for (long r0 = 0; r0 < nh && rc == RI_OK; r0 += chunk) {
     const long nn = std::min(chunk, nh - r0);
     mlp::features_half_kernel<<<mlp::nblk(nn), 256, 0, s>>>(gov, sys->eps, t2m, o, v, r0, nn, nm, X);
