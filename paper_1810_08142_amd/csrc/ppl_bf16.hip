@@ -58,6 +58,17 @@ __device__ inline void split_f32(float x, uint16_t& hi, uint16_t& lo) {
   lo = bf16_bits(x - bf16_val(hi));
 }
 
+// the split of two values, packed in a word each (the conversion instruction rounds to
+// nearest even too)
+__device__ inline uint32_t bf16_pair(float x, float y) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2_t{static_cast<__bf16>(x), static_cast<__bf16>(y)});
+}
+__device__ inline void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) {
+  hi = bf16_pair(x, y);
+  lo = bf16_pair(x - __builtin_bit_cast(float, hi << 16), y - __builtin_bit_cast(float, hi & 0xFFFF0000u));
+}
+
 __device__ inline f32x4_t mfma_bf16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -349,9 +360,9 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
 // tile as above (ab block pair x half h of cd block pair: 8 c by 16 d, the same 24
 // staged factor rows per Q step), but wave w computes only one of the two integrals,
 // g = w >> 2 (0: (ac|bd), 1: (ad|bc)), for 4 c by 8 d: c = 8h + 4(q >> 1) + i,
-// d = 8(q & 1) + j with q = w & 3.  Per Q step a wave then reads 24 fragments for 96
-// MFMAs instead of 32 (both integrals for 4 x 4 pairs), with the same 128 accumulator
-// registers.  Both integrals run one instruction stream: a wave's first operand is its
+// d = 8(j >> 2) + 4(q & 1) + (j & 3) with q = w & 3.  Per Q step a wave then reads 24
+// fragments for 96 MFMAs instead of 32 (both integrals for 4 x 4 pairs), with the same
+// 128 accumulator registers.  Both integrals run one instruction stream: a wave's first operand is its
 // c fragment, its second the d fragment; the (ac|bd) waves read the c rows at the a
 // columns and the d rows at the b columns and so hold element (a, b) of each tile,
 // the (ad|bc) waves read the c rows at the b columns and the d rows at the a columns
@@ -362,6 +373,18 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
 // so where both exist for one (a, b, c, d) they agree bit for bit.  The launch covers
 // cd block pairs pcd0 .. nbp-1; diagonal ab block pairs exit (the diagonal kernel
 // builds them).  Block 512.
+// Pipeline: a Q step is three chunks of eight factor rows (c 0-7 or 8-15; d 0-7; d 8-15),
+// 32 KB each, loaded straight to a ring of five LDS slots (all 160 KB).  A wave keeps the
+// step's c fragments in registers, reads the next ones while it works (with them the d pair
+// of the next 12 products), and there are two barriers per step: at j = 3 the c and the
+// first d chunk are used up, at j = 7 the second; the slots are then loaded again, at
+// least a whole step ahead of their use.  The products of the last d pair
+// before a barrier run after it, under the reads that follow.
+// Bound by the MFMA pipe at the clock that the power limit leaves (2.0 GHz): a step takes
+// 2.1 us of which 1.5 us are MFMAs; the epilogue and the first loads take 17 us per
+// workgroup, not overlapped.  At v = 512, Naux = 1536 250 ms, v = 256, Naux = 768 9.1 ms;
+// with the chunks staged through registers into three 48 KB slots (a barrier, the second
+// half's 48 KB written, another barrier) 287 and 10.5 ms.
 // Workgroup order: the workgroups of one ab block pair and a square tile of T x T cd
 // block pairs (c blocks by d blocks, both halves: 2T^2 workgroups, the tiles counted
 // triangularly from the tile row of pcd0's d block) form a group; consecutive groups
@@ -390,13 +413,14 @@ __device__ inline bool group_tile(int nb, long pcd0, long npairs, int ga, int T,
   return pcd >= pcd0;
 }
 
+constexpr int CHK = 8 * 2 * 32 * 4;  // runs of a chunk: eight factor rows (32 KB)
 __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh, const uint16_t* __restrict__ Bl,
                                                  int Qp, int vp, long slab0, long wts, int want_minus, long pcd0,
                                                  long npairs, int ga, int gt,
                                                  uint16_t* __restrict__ Wph, uint16_t* __restrict__ Wpl,
                                                  uint16_t* __restrict__ Wmh, uint16_t* __restrict__ Wml) {
-  __shared__ u32x4_t lds[3 * SLOT];
-  static_assert(3 * SLOT * 16 >= 4 * 32 * 4 * 64 * 4, "the ring holds the exchanged (ad|bc) tiles");
+  __shared__ u32x4_t lds[5 * CHK];
+  static_assert(5 * CHK * 16 >= 4 * 32 * 4 * 64 * 4, "the ring holds the exchanged (ad|bc) tiles");
   long pab_loc, pcd;
   int half;
   if (!group_tile(vp / TB, pcd0, npairs, ga, gt, pab_loc, pcd, half)) return;
@@ -408,39 +432,36 @@ __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh
   const int d_base = Db * TB;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
 
-  // staging: as in build_diag_body
+  // staging: a wave loads, of every factor row x of its parity, the 16 columns (a or b) of
+  // one of the split arrays: 1 KB, lane (e, run) from run (run ^ sw4(e)) of column e, to LDS
+  // in the order of the lanes
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int hl_w = (wave >> 1) & 1, xt = wave >> 2, e_t = (t >> 2) & 31, run_t = t & 3;
-  const int ag = e_t < 16 ? Ab * TB + e_t : Bb * TB + (e_t - 16);
+  const int hl_w = wave & 1, eb_w = (wave >> 1) & 1, xt = wave >> 2;
   const uint16_t* src = hl_w ? Bl : Bh;
-  const size_t xs = static_cast<size_t>(vp) * Qp;
+  const size_t xs = static_cast<size_t>(vp) * Qp;  // elements from one factor row to the next
   const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(src + static_cast<size_t>(c_base + xt) * xs), 0, -1, 0x00020000);
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(src + static_cast<size_t>(d_base + xt) * xs), 0, -1, 0x00020000);
-  const int voff = (ag * 32 + run_t * 8) * 2;
-  const int xsb2 = static_cast<int>(xs * 4);
-  const int l0 = xt * 256 + (hl_w * 32 + e_t) * 4 + (run_t ^ sw4(e_t));
-  auto gload = [&](u32x4_t* dst, int h2, int step) {
-    const int qb = step * vp * QC * 2;
+  const int voff = (((eb_w ? Bb : Ab) * TB + (lane >> 2)) * 32 + ((lane & 3) ^ sw4(lane >> 2)) * 8) * 2;
+  const int xsb2 = static_cast<int>(xs * 4);  // bytes for two factor rows
+  u32x4_t* const lw = lds + (xt * 2 + hl_w) * 128 + eb_w * 64;
+  const int nsteps = Qp / QC;
+  // row pairs k0 .. k1 - 1 of a chunk of a Q step: all c rows, or d rows 0 .. 3 and 8 .. 11,
+  // or (x2 = 2) 4 .. 7 and 12 .. 15
+  auto load = [&](const __amdgpu_buffer_rsrc_t& rs, int x2, int step, int slot, int k0, int k1) {
+    const int off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const int r = 6 * h2 + k;
-      dst[k] = __builtin_bit_cast(u32x4_t, r < 4 ? __builtin_amdgcn_raw_buffer_load_b128(rc, voff, r * xsb2 + qb, 0)
-                                                 : __builtin_amdgcn_raw_buffer_load_b128(rd, voff, (r - 4) * xsb2 + qb, 0));
-    }
+    for (int k = k0; k < k1; ++k)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lw + slot * CHK + k * 512),
+                                               16, voff, off + (x2 < 0 ? k : 2 * x2 + k) * xsb2, 0, 0);
   };
-  auto lstore = [&](const u32x4_t* sv, int slot) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) lds[slot * SLOT + l0 + 512 * k] = sv[k];
-  };
-  const int fe = lane & 15, frun = lane >> 4;
-  const int fsw = frun ^ sw4(fe);
+  const int fe = lane & 15, fsw = (lane >> 4) ^ sw4(fe);  // the same for e and e + 16 (sw4 reads bits 1..3)
   const int g = w >> 2, q = w & 3;
-  const int xc0 = (q >> 1) * 4, xd0 = 8 + (q & 1) * 8;
   // (ac|bd) reads the c rows at the a columns (e 0..15) and the d rows at the b columns
   // (e 16..31); (ad|bc) the c rows at the b columns and the d rows at the a columns
-  const int ec = g ? 16 : 0, ed = g ? 0 : 16;
+  const u32x4_t* const lc = lds + (q >> 1) * 4 * 256 + ((g ? 16 : 0) + fe) * 4 + fsw;
+  const u32x4_t* const ld = lds + (q & 1) * 4 * 256 + ((g ? 0 : 16) + fe) * 4 + fsw;
 
   f32x4_t o[4][8];
 #pragma unroll
@@ -448,67 +469,67 @@ __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int nsteps = Qp / QC;
-  // in a diagonal cd block pair the slots with c > d carry zero amplitudes: with c in the upper half and d in the
-  // lower one every pair of the wave has c > d.  Such a wave runs the same products (a
-  // branch around them costs the loop its schedule) and stores zeros.
-  const bool zero_w = Cb == Db && half == 1 && (q & 1) == 0;
+  // in a diagonal cd block pair the slots with c > d carry zero amplitudes: with c in the
+  // upper half and d in the lower one every pair of the wave has c > d.  Such a wave runs
+  // the same products (a branch around them costs the loop its schedule) and stores zeros.
+  const bool zero_w = Cb == Db && half == 1;
   {
-    auto compute = [&](int s0, int s1) {
-      auto frag = [&](int x, int hl, int e_off) -> bf16x8_t {
-        const int base = x < 12 ? s0 * SLOT : s1 * SLOT;
-        const int xx = x < 12 ? x : x - 12;
-        const u32x4_t v = lds[base + ((xx * 2 + hl) * 32 + e_off + fe) * 4 + fsw];
-        return __builtin_bit_cast(bf16x8_t, v);
-      };
-      bf16x8_t cf[4][2];
+    bf16x8_t cf[2][4][2], df[2][2];
+    auto next = [](int slot, int by) { return slot + by >= 5 ? slot + by - 5 : slot + by; };
+    auto read_c = [&](bf16x8_t(&f)[4][2], int slot, int i) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int hl = 0; hl < 2; ++hl) f[i][hl] = __builtin_bit_cast(bf16x8_t, lc[slot * CHK + (i * 2 + hl) * 128]);
+    };
+    auto read_d = [&](bf16x8_t(&f)[2], int slot, int j) {  // j = 0..3 of the chunk
 #pragma unroll
-        for (int hl = 0; hl < 2; ++hl) cf[i][hl] = frag(xc0 + i, hl, ec);
+      for (int hl = 0; hl < 2; ++hl) f[hl] = __builtin_bit_cast(bf16x8_t, ld[slot * CHK + (j * 2 + hl) * 128]);
+    };
+    int sc = 0;  // slot of the step's c rows; its d rows follow in the ring
+    load(rc, -1, 0, 0, 0, 4);
+    load(rd, 0, 0, 1, 0, 4);
+    load(rd, 2, 0, 2, 0, 4);
+    load(rc, -1, 1, 3, 0, 4);
+    stage_barrier<8>();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) read_c(cf[0], 0, i);
+    read_d(df[0], 1, 0);
+    // Loads are issued C0 D0 D0' C1 | D1 D1' C2 | D2 ... (D, D': the two chunks of d rows), a
+    // few with every group of products.
+    load(rd, 0, 1, 4, 0, 1);
+    auto step = [&](int st, bf16x8_t(&c0)[4][2], bf16x8_t(&c1)[4][2]) {
+      const int s1 = next(sc, 1), s2 = next(sc, 2), s3 = next(sc, 3), s4 = next(sc, 4);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const bf16x8_t dh = frag(xd0 + j, 0, ed), dl = frag(xd0 + j, 1, ed);
+        // j = 3: D' of this step and C of the next are there, this step's C and D used up;
+        // j = 7: D of the next step is there, this step's D' used up
+        if (j == 3) stage_barrier<4>();
+        if (j == 7) stage_barrier<8>();
+        read_d(df[(j + 1) & 1], j < 3 ? s1 : j < 7 ? s2 : s4, (j + 1) & 3);
+        if (j >= 3 && j < 7) read_c(c1, s3, j - 3);
+        if (j == 7) load(rd, 0, st + 2, s2, 0, 1);
+        if (j < 3) load(rd, 0, st + 1, s4, j + 1, j + 2);
+        if (j == 3) load(rd, 2, st + 1, sc, 0, 2);
+        if (j == 4) load(rd, 2, st + 1, sc, 2, 4);
+        if (j == 5) load(rc, -1, st + 2, s1, 0, 2);
+        if (j == 6) load(rc, -1, st + 2, s1, 2, 4);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i][j] = mfma3(cf[i][0], cf[i][1], dh, dl, o[i][j]);
-      }
-      // issue order: the c fragments and the first d pair, then per d the 12 products
-      // with the next d pair's reads ahead of them
-      __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);
+        for (int i = 0; i < 4; ++i) o[i][j] = mfma_bf16(c0[i][0], df[j & 1][1], o[i][j]);
 #pragma unroll
-      for (int j = 0; j < 7; ++j) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        for (int i = 0; i < 4; ++i) o[i][j] = mfma_bf16(c0[i][1], df[j & 1][0], o[i][j]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i][j] = mfma_bf16(c0[i][0], df[j & 1][0], o[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
+      sc = s3;
     };
-    u32x4_t sa[6], sb[6];
-    gload(sa, 0, 0);
-    gload(sb, 1, 0);
-    lstore(sa, 0);
-    lstore(sb, 1);
-    if (nsteps > 1) {
-      gload(sa, 0, 1);
-      gload(sb, 1, 1);
+    int st = 0;
+    for (; st + 2 <= nsteps; st += 2) {
+      step(st, cf[0], cf[1]);
+      step(st + 1, cf[1], cf[0]);
     }
-    __syncthreads();
-    int s0 = 0;
-    for (int st = 0; st < nsteps; ++st) {
-      const int s1 = s0 == 2 ? 0 : s0 + 1, sf = s1 == 2 ? 0 : s1 + 1;
-      const bool more = st + 1 < nsteps;
-      if (more) {
-        lstore(sa, sf);
-        if (st + 2 < nsteps) gload(sa, 0, st + 2);
-      }
-      compute(s0, s1);
-      __syncthreads();
-      if (more) {
-        lstore(sb, s0);
-        if (st + 2 < nsteps) gload(sb, 1, st + 2);
-        __syncthreads();
-      }
-      s0 = sf;
-    }
+    if (st < nsteps) step(st, cf[0], cf[1]);
+    stage_barrier<0>();  // no load is left to land in the ring
   }
 
   // exchange: the (ad|bc) wave q stores its tiles at [q][i][j][r][lane] (floats), the
@@ -547,38 +568,31 @@ __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh
     const size_t row = static_cast<size_t>(pab_loc) * 256 + a_in * 16 + b_in;
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
-      const int ow = 4 * (q >> 1) + 2 * (q & 1) + jb;
+      const int ow = 4 * (q >> 1) + 2 * jb + (q & 1);
       const size_t slot0 = static_cast<size_t>(pcd) * 256 + half * 128 + ow * 16;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        uint16_t ph[8], pl[8], mh[8], ml[8];
+        u32x4_t ph, pl, mh, ml;
 #pragma unroll
-        for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-          for (int j2 = 0; j2 < 4; ++j2) {
-            const int i = 2 * hh + i2, j = 4 * jb + j2;
-            const float v1 = zero_w ? 0.f : o[i][j][r], v2 = zero_w ? 0.f : xval(i, j, r);
-            split_f32(v1 + v2, ph[i2 * 4 + j2], pl[i2 * 4 + j2]);
-            split_f32(v1 - v2, mh[i2 * 4 + j2], ml[i2 * 4 + j2]);
-          }
-        u32x4_t h, l;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          h[k] = static_cast<uint32_t>(ph[2 * k]) | (static_cast<uint32_t>(ph[2 * k + 1]) << 16);
-          l[k] = static_cast<uint32_t>(pl[2 * k]) | (static_cast<uint32_t>(pl[2 * k + 1]) << 16);
+        for (int k2 = 0; k2 < 4; ++k2) {
+          const int i = 2 * hh + (k2 >> 1), j = 4 * jb + 2 * (k2 & 1);
+          const float v1 = zero_w && !jb ? 0.f : o[i][j][r], v2 = zero_w && !jb ? 0.f : xval(i, j, r);
+          const float u1 = zero_w && !jb ? 0.f : o[i][j + 1][r], u2 = zero_w && !jb ? 0.f : xval(i, j + 1, r);
+          uint32_t hi, lo;
+          split_pair(v1 + v2, u1 + u2, hi, lo);
+          ph[k2] = hi;
+          pl[k2] = lo;
+          split_pair(v1 - v2, u1 - u2, hi, lo);
+          mh[k2] = hi;
+          ml[k2] = lo;
         }
         const size_t k = slot0 + 8 * hh;
         const size_t at = k / KB * wts + row * KB + k % KB;
-        *reinterpret_cast<u32x4_t*>(Wph + at) = h;
-        *reinterpret_cast<u32x4_t*>(Wpl + at) = l;
+        *reinterpret_cast<u32x4_t*>(Wph + at) = ph;
+        *reinterpret_cast<u32x4_t*>(Wpl + at) = pl;
         if (want_minus) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            h[k] = static_cast<uint32_t>(mh[2 * k]) | (static_cast<uint32_t>(mh[2 * k + 1]) << 16);
-            l[k] = static_cast<uint32_t>(ml[2 * k]) | (static_cast<uint32_t>(ml[2 * k + 1]) << 16);
-          }
-          *reinterpret_cast<u32x4_t*>(Wmh + at) = h;
-          *reinterpret_cast<u32x4_t*>(Wml + at) = l;
+          *reinterpret_cast<u32x4_t*>(Wmh + at) = mh;
+          *reinterpret_cast<u32x4_t*>(Wml + at) = ml;
         }
       }
     }

@@ -80,6 +80,13 @@ inline long device_cus() {
   return 256;
 }
 
+// Workgroup barrier once this wave's LDS accesses are done and at most N of its newest
+// vector memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // Workgroups of kernel f (block threads each) resident on the current device at once:
 // blocks per CU by the runtime's occupancy rule (registers, LDS, waves) times the CU
 // count, or 256 * dflt_per_cu where the runtime gives no answer (no device).
