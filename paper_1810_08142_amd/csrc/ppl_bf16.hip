@@ -12,10 +12,11 @@
 //   Bh/Bl [c][Q/32][a][32] factors in Q tiles of 32 (Q padded to 32): one 16-byte run
 //                          holds the 8 consecutive Q a lane feeds to one MFMA, and the
 //                          16 columns of one block read in a Q step are one 1 KB run
-//   Th/Tl [slot/32][ij][32]       packed tau+- (or tau-) in tiles of 32 slots
-//   Wh/Wl [slot/32][ab slot][32]  build output, already split, in tiles of 32 slots
-// The contraction reads one tile (32 slots of a 256-row block, 16 KB per array) per k
-// step as one contiguous run.
+//   Th/Tl [slot/32][ij/16][(slot/8)%4][ij%16][slot%8]  packed tau+- in tiles of 32 slots
+//   Wh/Wl the same with ab slots for ij: build output, already split
+// A 1 KB block of 16 rows is one MFMA operand in the order of its lanes: the build stores
+// 256 bytes in a row, and the contraction reads one tile (32 slots of a 256-row block,
+// 16 KB per array) per k step as one contiguous run that it can load straight to LDS.
 // Within a cd block pair the 256 slots are ordered so that the 16 (c, d) pairs one
 // wave of the build owns are consecutive: slot = half*128 + wave*16 + i*4 + j with
 // c = 8*half + 4*(wave>>2) + i, d = 4*(wave&3) + j.  A lane then stores its 16 results
@@ -25,6 +26,7 @@
 // element k%8; B[k][n] at lane n + 16*(k/8), element k%8; D[m][n] at lane
 // n + 16*(m/4), element m%4.
 #include <cstdint>
+#include <type_traits>
 
 #include "ppl_shared.h"
 
@@ -39,6 +41,12 @@ constexpr int QC = 32;  // RI functions per build step (= MFMA K)
 constexpr int KB = 32;  // cd slots per contraction step (= MFMA K)
 constexpr int CBM = 256;  // contraction tile rows
 constexpr int CNT = 2 * CBM;  // contraction threads: CBM / 32 waves of 32 rows each
+
+// Element (row, k % 32) of a tile of 32 k: rows in blocks of 16, and a block's 1 KB in the
+// order of an MFMA operand's lanes, [k/8][row % 16][k % 8].
+__host__ __device__ inline size_t tile_at(size_t row, int k) {
+  return row / 16 * 512 + k / 8 * 128 + row % 16 * 8 + k % 8;
+}
 
 __host__ __device__ inline uint16_t bf16_bits(float f) {
   // round to nearest even (inputs are finite)
@@ -119,42 +127,56 @@ __global__ __launch_bounds__(256) void split_b_kernel(const double* __restrict__
 }
 
 // ---------------------------------------------------------------- split pack
-// Th/Tl[k/32][col][k%32] with k = pcd*256 + slot: sign > 0 tau+ (with the 1/2 on c == d)
-// over i<=j columns, sign < 0 tau- over i<j columns; both from the pair-symmetric part of
-// tau.  grid (nbp, ncol), block 256
+// Th/Tl (tiles of 32 slots, columns by rows) with k = pcd*256 + slot: sign > 0 tau+ (with
+// the 1/2 on c == d) over i<=j columns, sign < 0 tau- over i<j columns; both from the
+// pair-symmetric part of tau.  One workgroup packs sixteen columns, so that it writes whole
+// 1 KB blocks.  grid (nbp, ncol/16), block 256
 __global__ __launch_bounds__(256) void pack_tau_bf16_kernel(const double* __restrict__ tau, int o, int v,
                                                             int sign, uint16_t* __restrict__ Th,
                                                             uint16_t* __restrict__ Tl) {
+  __shared__ uint16_t sh[2][16][256 + 8];
   int Cb, Db;
   tri_decode(blockIdx.x, Cb, Db);
-  const int col = blockIdx.y, slot = threadIdx.x;
+  const int slot = threadIdx.x;
   int c_in, d_in;
   slot_cd(slot, c_in, d_in);
   const int c = Cb * TB + c_in, d = Db * TB + d_in;
   const int nreal = sign > 0 ? o * (o + 1) / 2 : o * (o - 1) / 2;
-  double val = 0.0;
-  if (d < v && (Cb < Db || c_in <= d_in) && (sign > 0 || c != d) && col < nreal) {
-    int i, j;
-    tri_decode(col, i, j);
-    if (sign < 0) j += 1;
-    const size_t vv = static_cast<size_t>(v) * v;
-    const double* tij = tau + (static_cast<size_t>(i) * o + j) * vv;
-    const double* tji = tau + (static_cast<size_t>(j) * o + i) * vv;
-    const size_t cd = static_cast<size_t>(c) * v + d, dc = static_cast<size_t>(d) * v + c;
-    const double x1 = tij[cd], x2 = tij[dc], x3 = tji[cd], x4 = tji[dc];
-    if (sign > 0) {
-      val = 0.25 * ((x1 + x4) + (x2 + x3));
-      if (c == d) val *= 0.5;
-    } else {
-      val = 0.25 * ((x1 + x4) - (x2 + x3));
+  const bool live = d < v && (Cb < Db || c_in <= d_in) && (sign > 0 || c != d);
+  const size_t vv = static_cast<size_t>(v) * v;
+  const size_t cd = static_cast<size_t>(c) * v + d, dc = static_cast<size_t>(d) * v + c;
+#pragma unroll 4
+  for (int cc = 0; cc < 16; ++cc) {
+    const int col = blockIdx.y * 16 + cc;
+    double val = 0.0;
+    if (live && col < nreal) {
+      int i, j;
+      tri_decode(col, i, j);
+      if (sign < 0) j += 1;
+      const double* tij = tau + (static_cast<size_t>(i) * o + j) * vv;
+      const double* tji = tau + (static_cast<size_t>(j) * o + i) * vv;
+      const double x1 = tij[cd], x2 = tij[dc], x3 = tji[cd], x4 = tji[dc];
+      if (sign > 0) {
+        val = 0.25 * ((x1 + x4) + (x2 + x3));
+        if (c == d) val *= 0.5;
+      } else {
+        val = 0.25 * ((x1 + x4) - (x2 + x3));
+      }
     }
+    split_f64(val, sh[0][cc][slot], sh[1][cc][slot]);
   }
-  uint16_t hi, lo;
-  split_f64(val, hi, lo);
-  const size_t k = static_cast<size_t>(blockIdx.x) * 256 + slot;
-  const size_t idx = (k / KB * gridDim.y + col) * KB + k % KB;
-  Th[idx] = hi;
-  Tl[idx] = lo;
+  __syncthreads();
+  // eight blocks of [k/8][column][8] per array: thread t takes runs t and t + 256
+#pragma unroll
+  for (int hl = 0; hl < 2; ++hl)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int id = threadIdx.x + 256 * h, kt = id >> 6, run = (id >> 4) & 3, cc = id & 15;
+      const u32x4_t x = *reinterpret_cast<const u32x4_t*>(&sh[hl][cc][kt * 32 + run * 8]);
+      const size_t at = (static_cast<size_t>(blockIdx.x) * 8 + kt) * (static_cast<size_t>(gridDim.y) * 16 * KB) +
+                        static_cast<size_t>(blockIdx.y) * 512 + (id & 63) * 8;
+      *reinterpret_cast<u32x4_t*>((hl ? Tl : Th) + at) = x;
+    }
 }
 
 // ---------------------------------------------------------------- build
@@ -341,7 +363,7 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
         l[k] = static_cast<uint32_t>(pl[2 * k]) | (static_cast<uint32_t>(pl[2 * k + 1]) << 16);
       }
       const size_t k = slot0 + 8 * hh;
-      const size_t at = k / KB * wts + row * KB + k % KB;
+      const size_t at = k / KB * wts + tile_at(row, static_cast<int>(k % KB));
       *reinterpret_cast<u32x4_t*>(Wph + at) = h;
       *reinterpret_cast<u32x4_t*>(Wpl + at) = l;
       if (want_minus) {
@@ -381,10 +403,11 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
 // least a whole step ahead of their use.  The products of the last d pair
 // before a barrier run after it, under the reads that follow.
 // Bound by the MFMA pipe at the clock that the power limit leaves (2.0 GHz): a step takes
-// 2.1 us of which 1.5 us are MFMAs; the epilogue and the first loads take 17 us per
-// workgroup, not overlapped.  At v = 512, Naux = 1536 250 ms, v = 256, Naux = 768 9.1 ms;
-// with the chunks staged through registers into three 48 KB slots (a barrier, the second
-// half's 48 KB written, another barrier) 287 and 10.5 ms.
+// 2.1 us of which 1.5 us are MFMAs; the epilogue and the first loads take about 10 us per
+// workgroup, not overlapped.  At v = 512, Naux = 1536 234 ms, v = 256, Naux = 768 8.1 ms
+// (250 and 9.1 ms with W rows of 64 bytes, of which a store filled 16; 287 and 10.5 ms with
+// the chunks staged through registers into three 48 KB slots: a barrier, the second half's
+// 48 KB written, another barrier).
 // Workgroup order: the workgroups of one ab block pair and a square tile of T x T cd
 // block pairs (c blocks by d blocks, both halves: 2T^2 workgroups, the tiles counted
 // triangularly from the tile row of pcd0's d block) form a group; consecutive groups
@@ -587,7 +610,7 @@ __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh
           ml[k2] = lo;
         }
         const size_t k = slot0 + 8 * hh;
-        const size_t at = k / KB * wts + row * KB + k % KB;
+        const size_t at = k / KB * wts + tile_at(row, static_cast<int>(k % KB));
         *reinterpret_cast<u32x4_t*>(Wph + at) = ph;
         *reinterpret_cast<u32x4_t*>(Wpl + at) = pl;
         if (want_minus) {
@@ -614,57 +637,38 @@ __global__ __launch_bounds__(512) void build_w_bf16x3_diag(const uint16_t* __res
 }
 
 // ---------------------------------------------------------------- contract
-// C[m][n] (+)= sum_k W[m][k] T[n][k], both split and stored in tiles of KB k: element
-// (m, k) of W at (k / KB) * lda + m * KB + k % KB (lda: elements from one tile to the
-// next), of T likewise with ldb; tile
-// CBM (m) x 16*NTW (n); CBM/32 waves, wave w owns rows 32w..32w+31 (two m tiles) and all
-// columns.  LDS holds 16-byte runs [row][8 runs: hl 2 x run 4], run index XOR-swizzled
-// with sw8(row).  The k range may be split over grid.z: split z sums k in
-// [z*kz, min(K, (z+1)*kz)) into C + z*zs.  accum adds into C instead of writing it.
-// grid (ncol/(16*NTW), rows/CBM, splits), block CNT
+// C[m][n] (+)= sum_k W[m][k] T[n][k], both split and stored in tiles of KB k (tile_at; lda,
+// ldb: elements from one tile to the next); tile CBM (m) x 16*NTW (n); CBM/32 waves, wave w
+// owns rows 32w..32w+31 (two m tiles) and all columns.  A wave reads its own A fragments
+// from memory, one step ahead; the B fragments are shared, loaded straight to a ring of two
+// LDS stages [tile][hl][lane], also one step ahead, each pair read from LDS ahead of the
+// products of the one before it (the first of a step before the last products of the step
+// before, after the one barrier per step).  The k range may be split over grid.z: split z
+// sums k in [z*kz, min(K, (z+1)*kz)) into C + z*zs.  accum adds into C instead of writing
+// it.  Bound by the LDS reads of B (each wave reads all of it) and the MFMA pipe: 144
+// columns, o = 16, v = 256, 0.94 ms (1.19 ms with both operands staged through registers,
+// rows of 64 bytes).  grid (ncol/(16*NTW), rows/CBM, splits), block CNT
 template <int NTW>
-__global__ __launch_bounds__(CNT) void contract_bf16x3(const uint16_t* __restrict__ Wh, const uint16_t* __restrict__ Wl,
-                                                       long lda, const uint16_t* __restrict__ Th,
-                                                       const uint16_t* __restrict__ Tl, long ldb, long K, int ncol,
-                                                       float* __restrict__ C, long kz, long zs, int accum) {
-  constexpr int BN = 16 * NTW;
-  constexpr int ARUNS = CBM * 2 * 4, BRUNS = BN * 2 * 4;
-  __shared__ u32x4_t sA[2 * ARUNS];
-  __shared__ u32x4_t sB[2 * BRUNS];
+__global__ __launch_bounds__(CNT) __attribute__((amdgpu_waves_per_eu(2))) void contract_bf16x3(
+    const uint16_t* __restrict__ Wh, const uint16_t* __restrict__ Wl, long lda, const uint16_t* __restrict__ Th,
+    const uint16_t* __restrict__ Tl, long ldb, long K, int ncol, float* __restrict__ C, long kz, long zs, int accum) {
+  constexpr int BN = 16 * NTW, NB = 2 * NTW, NBW = (NB + 7) / 8;  // B blocks of 1 KB, per wave
+  static_assert(CNT == 512, "eight waves");
+  __shared__ u32x4_t sB[2 * NB * 64];
   unsigned tx, ty;
   xcd_tile(tx, ty);
   const long n0 = static_cast<long>(tx) * BN, m0 = static_cast<long>(ty) * CBM;
-  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   // this split's k range (every split holds at least one step)
   const long k_lo = blockIdx.z * kz;
   const long k_len = (K < k_lo + kz ? K : k_lo + kz) - k_lo;
   C += blockIdx.z * zs;
-
-  // staging: A 8*CBM runs (4 per thread), B 8*BN runs (BPER per thread, the last may idle)
-  constexpr int BPER = (BRUNS + CNT - 1) / CNT;
-  size_t aoff[4];
-  int alo[4];
-  const uint16_t* asrc[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int id = t + CNT * r;
-    const int row = id >> 3, hl = (id >> 2) & 1, run = id & 3;
-    asrc[r] = hl ? Wl : Wh;
-    aoff[r] = static_cast<size_t>(k_lo / KB) * lda + static_cast<size_t>(m0 + row) * KB + run * 8;
-    alo[r] = row * 8 + ((hl * 4 + run) ^ sw8(row));
-  }
-  size_t boff[BPER];
-  int blo[BPER];
-  const uint16_t* bsrc[BPER];
-#pragma unroll
-  for (int r = 0; r < BPER; ++r) {
-    const int id = t + CNT * r;
-    const int row = (id >> 3) < BN ? (id >> 3) : 0, hl = (id >> 2) & 1, run = id & 3;
-    bsrc[r] = hl ? Tl : Th;
-    boff[r] = static_cast<size_t>(k_lo / KB) * ldb + static_cast<size_t>(n0 + row) * KB + run * 8;
-    blo[r] = id < BRUNS ? row * 8 + ((hl * 4 + run) ^ sw8(row)) : -1;
-  }
-  const int fr = lane & 15, frun = lane >> 4;
+  const long nsteps = k_len / KB, last = nsteps - 1;
+  const uint16_t* const ah = Wh + k_lo / KB * lda + (m0 / 16 + 2 * w) * 512;
+  const uint16_t* const al = Wl + k_lo / KB * lda + (m0 / 16 + 2 * w) * 512;
+  const uint16_t* const bh = Th + k_lo / KB * ldb + n0 / 16 * 512;
+  const uint16_t* const bl = Tl + k_lo / KB * ldb + n0 / 16 * 512;
+  const int lo16 = lane * 16;
 
   f32x4_t acc[2][NTW];
 #pragma unroll
@@ -672,56 +676,69 @@ __global__ __launch_bounds__(CNT) void contract_bf16x3(const uint16_t* __restric
 #pragma unroll
     for (int u = 0; u < NTW; ++u) acc[i][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const long nsteps = k_len / KB;
-  u32x4_t ra[4], rb[BPER];
+  bf16x8_t ra[2][2][2], bf[2][2];
+  // past the last step: loaded again, not used
+  auto aload = [&](bf16x8_t(&f)[2][2], long st) {
+    const long ko = min(st, last) * lda;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) ra[r] = *reinterpret_cast<const u32x4_t*>(asrc[r] + aoff[r]);
+    for (int hl = 0; hl < 2; ++hl) {
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>((hl ? al : ah) + ko), 0, -1, 0x00020000);
 #pragma unroll
-  for (int r = 0; r < BPER; ++r)
-    if (blo[r] >= 0) rb[r] = *reinterpret_cast<const u32x4_t*>(bsrc[r] + boff[r]);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) sA[alo[r]] = ra[r];
-#pragma unroll
-  for (int r = 0; r < BPER; ++r)
-    if (blo[r] >= 0) sB[blo[r]] = rb[r];
-  __syncthreads();
-  for (long st = 0; st < nsteps; ++st) {
-    const int ab = (st & 1) * ARUNS, bb = (st & 1) * BRUNS;
-    const bool more = st + 1 < nsteps;
-    if (more) {
-      const size_t ka = static_cast<size_t>(st + 1) * lda, kb = static_cast<size_t>(st + 1) * ldb;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ra[r] = *reinterpret_cast<const u32x4_t*>(asrc[r] + aoff[r] + ka);
-#pragma unroll
-      for (int r = 0; r < BPER; ++r)
-        if (blo[r] >= 0) rb[r] = *reinterpret_cast<const u32x4_t*>(bsrc[r] + boff[r] + kb);
+      for (int i = 0; i < 2; ++i)
+        f[i][hl] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rs, lo16, 1024 * i, 0));
     }
-    bf16x8_t a[2][2];
+  };
+  auto bload = [&](long st, int slot) {
+    const long ko = min(st, last) * ldb;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int r = 0; r < NBW; ++r) {
+      const int b = min(w + 8 * r, NB - 1);  // (tile, hl); the last block again where none is left
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<uint16_t*>(((b & 1) ? bl : bh) + ko + (b >> 1) * 512), 0, -1, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sB + (slot * NB + b) * 64),
+                                               16, lo16, 0, 0, 0);
+    }
+  };
+  auto bread = [&](bf16x8_t(&f)[2], int slot, int u) {
 #pragma unroll
-      for (int hl = 0; hl < 2; ++hl) {
-        const int row = w * 32 + i * 16 + fr;
-        a[i][hl] = __builtin_bit_cast(bf16x8_t, sA[ab + row * 8 + ((hl * 4 + frun) ^ sw8(row))]);
-      }
+    for (int hl = 0; hl < 2; ++hl) f[hl] = __builtin_bit_cast(bf16x8_t, sB[(slot * NB + u * 2 + hl) * 64 + lane]);
+  };
+  bload(0, 0);
+  aload(ra[0], 0);
+  bload(1, 1);
+  stage_barrier<4 + NBW>();
+  bread(bf[0], 0, 0);
+  auto step = [&](long st, auto parity) {
+    constexpr int P = decltype(parity)::value, Q0 = (NTW & 1) ? P : 0;  // first fragment of the step
+    aload(ra[P ^ 1], st + 1);
 #pragma unroll
     for (int u = 0; u < NTW; ++u) {
-      const int row = u * 16 + fr, sw = sw8(row);
-      const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, sB[bb + row * 8 + ((0 * 4 + frun) ^ sw)]);
-      const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, sB[bb + row * 8 + ((1 * 4 + frun) ^ sw)]);
+      const int q = (Q0 + u) & 1;
+      if (u + 1 < NTW) {
+        bread(bf[q ^ 1], P, u + 1);
+      } else {
+        stage_barrier<4>();  // the next step's B is there, this step's used up
+        bload(st + 2, P);
+        bread(bf[q ^ 1], P ^ 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) acc[i][u] = mfma3(a[i][0], a[i][1], bh, bl, acc[i][u]);
+      for (int i = 0; i < 2; ++i) acc[i][u] = mfma_bf16(ra[P][i][0], bf[q][1], acc[i][u]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][u] = mfma_bf16(ra[P][i][1], bf[q][0], acc[i][u]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][u] = mfma_bf16(ra[P][i][0], bf[q][0], acc[i][u]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (more) {
-      const int na = ((st + 1) & 1) * ARUNS, nbb = ((st + 1) & 1) * BRUNS;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sA[na + alo[r]] = ra[r];
-#pragma unroll
-      for (int r = 0; r < BPER; ++r)
-        if (blo[r] >= 0) sB[nbb + blo[r]] = rb[r];
-    }
-    __syncthreads();
+  };
+  long st = 0;
+  for (; st + 2 <= nsteps; st += 2) {
+    step(st, std::integral_constant<int, 0>{});
+    step(st + 1, std::integral_constant<int, 1>{});
   }
+  if (st < nsteps) step(st, std::integral_constant<int, 0>{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load is left to land in LDS
   // D[m][n]: lane n + 16*(m/4), element m%4
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -739,100 +756,117 @@ __global__ __launch_bounds__(CNT) void contract_bf16x3(const uint16_t* __restric
 // rows by four columns; wave (wr, wc) owns rows 128 wr .. 128 wr + 127 and columns
 // 16 NSUB wc .. + 16 NSUB - 1 (8 x NSUB MFMA tiles), so per k step it reads 16 A and
 // 2 NSUB B fragments for 24 NSUB MFMAs (the row strips above read 4 and 2 NTW for 6 NTW).
-// LDS holds 16-byte runs [row][8 runs: hl 2 x run 4] as above, double-buffered, but
-// with run q of row m at q ^ ((m >> 1) & 7): the sixteen rows of one fragment read still
-// hit distinct bank groups, and the swizzle repeats every 16 rows, so the fragments of
-// different row tiles lie at constant offsets from one address.  Operands are tiled as
-// for contract_bf16x3, and every tile sums its k steps in the same order.
+// Both operands are loaded straight to LDS, [tile][hl][lane]: A (from HBM) up to two steps
+// ahead into a ring of three stages, B (which the caches hold) one step ahead into a ring of
+// two.  One barrier per step, at i = 7, where the step's last A pair is in registers; the
+// next step's B fragments and first A pair are read there, before the last products run.
+// Operands are tiled as for contract_bf16x3, and every tile sums its k steps in the same
+// order.  Bound by the MFMA pipe (60% busy): o = 32, v = 512 4.6 ms (192 columns) and 4.1 ms
+// (256 columns) per slab, 5.9 and 5.1 ms with the operands staged through registers.
 // grid (ncol/(64 NSUB), rows/256, splits), block 512
 template <int NSUB>
 __global__ __launch_bounds__(512) void contract2_bf16x3(const uint16_t* __restrict__ Wh, const uint16_t* __restrict__ Wl,
                                                         long lda, const uint16_t* __restrict__ Th,
                                                         const uint16_t* __restrict__ Tl, long ldb, long K, int ncol,
                                                         float* __restrict__ C, long kz, long zs, int accum) {
-  constexpr int BM = 256, BN = 64 * NSUB, NT = 512;
-  constexpr int ARUNS = BM * 8, BRUNS = BN * 8, APER = ARUNS / NT, BPER = BRUNS / NT;
-  __shared__ u32x4_t sA[2 * ARUNS];
-  __shared__ u32x4_t sB[2 * BRUNS];
+  constexpr int BM = 256, BN = 64 * NSUB;
+  constexpr int AST = BM / 16 * 2 * 64, BST = BN / 16 * 2 * 64;  // runs of a stage
+  // one array: with two, the compiler waits for every load to LDS before the next LDS read
+  __shared__ u32x4_t lds[3 * AST + 2 * BST];
+  u32x4_t* const sA = lds;
+  u32x4_t* const sB = lds + 3 * AST;
   unsigned tx, ty;
   xcd_tile(tx, ty);
   const long n0 = static_cast<long>(tx) * BN, m0 = static_cast<long>(ty) * BM;
-  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   const int wr = w >> 2, wc = w & 3;
   const long k_lo = blockIdx.z * kz;
   const long k_len = (K < k_lo + kz ? K : k_lo + kz) - k_lo;
   C += blockIdx.z * zs;
-
-  // staging: run id t + 512 r is row t/8 + 64 r of the tile, with the thread's own hi/lo
-  // array and 8-element run; sw8 of the row does not depend on r
-  const int srow = t >> 3, shl = (t >> 2) & 1, srun = t & 3;
-  const uint16_t* ap = (shl ? Wl : Wh) + static_cast<size_t>(k_lo / KB) * lda + static_cast<size_t>(m0 + srow) * KB + srun * 8;
-  const uint16_t* bp = (shl ? Tl : Th) + static_cast<size_t>(k_lo / KB) * ldb + static_cast<size_t>(n0 + srow) * KB + srun * 8;
-  constexpr int astep = 64 * KB, bstep = 64 * KB;  // 64 rows on
-  auto sw = [](int m) { return (m >> 1) & 7; };
-  const int slo = srow * 8 + ((shl * 4 + srun) ^ sw(srow));  // + 512 r
-  const int fr = lane & 15, frun = lane >> 4;
+  const long nsteps = k_len / KB, last = nsteps - 1;
+  // a wave loads the hi or lo blocks (w & 1) of four row tiles and of NSUB column tiles
+  const uint16_t* const ap = ((w & 1) ? Wl : Wh) + k_lo / KB * lda + (m0 / 16 + (w >> 1) * 4) * 512;
+  const uint16_t* const bp = ((w & 1) ? Tl : Th) + k_lo / KB * ldb + (n0 / 16 + (w >> 1) * NSUB) * 512;
+  u32x4_t* const la = sA + ((w >> 1) * 8 + (w & 1)) * 64;
+  u32x4_t* const lb = sB + ((w >> 1) * 2 * NSUB + (w & 1)) * 64;
+  // tiles r0 .. r1 - 1 of a step (past the last one: loaded again, not used)
+  auto aload = [&](long st, int slot, int r0, int r1) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(ap + min(st, last) * lda), 0, -1, 0x00020000);
+#pragma unroll
+    for (int r = r0; r < r1; ++r)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (__attribute__((address_space(3))) void*)(la + slot * AST + r * 128), 16, lane * 16, r * 1024, 0, 0);
+  };
+  auto bload = [&](long st, int slot) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(bp + min(st, last) * ldb), 0, -1, 0x00020000);
+#pragma unroll
+    for (int r = 0; r < NSUB; ++r)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (__attribute__((address_space(3))) void*)(lb + slot * BST + r * 128), 16, lane * 16, r * 1024, 0, 0);
+  };
 
   f32x4_t acc[8][NSUB];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int u = 0; u < NSUB; ++u) acc[i][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  const long nsteps = k_len / KB;
-  u32x4_t ra[APER], rb[BPER];
+  bf16x8_t bf[2][NSUB][2], af[2][2];
+  auto bread = [&](bf16x8_t(&f)[NSUB][2], int slot) {
 #pragma unroll
-  for (int r = 0; r < APER; ++r) ra[r] = *reinterpret_cast<const u32x4_t*>(ap + r * astep);
+    for (int u = 0; u < NSUB; ++u)
 #pragma unroll
-  for (int r = 0; r < BPER; ++r) rb[r] = *reinterpret_cast<const u32x4_t*>(bp + r * bstep);
+      for (int hl = 0; hl < 2; ++hl)
+        f[u][hl] = __builtin_bit_cast(bf16x8_t, sB[slot * BST + ((wc * NSUB + u) * 2 + hl) * 64 + lane]);
+  };
+  auto aread = [&](bf16x8_t(&f)[2], int slot, int i) {
 #pragma unroll
-  for (int r = 0; r < APER; ++r) sA[slo + 512 * r] = ra[r];
-#pragma unroll
-  for (int r = 0; r < BPER; ++r) sB[slo + 512 * r] = rb[r];
-  __syncthreads();
-  for (long st = 0; st < nsteps; ++st) {
-    const int ab = (st & 1) * ARUNS, bb = (st & 1) * BRUNS;
-    const bool more = st + 1 < nsteps;
-    if (more) {
-      const size_t ka = static_cast<size_t>(st + 1) * lda, kb = static_cast<size_t>(st + 1) * ldb;
-#pragma unroll
-      for (int r = 0; r < APER; ++r) ra[r] = *reinterpret_cast<const u32x4_t*>(ap + r * astep + ka);
-#pragma unroll
-      for (int r = 0; r < BPER; ++r) rb[r] = *reinterpret_cast<const u32x4_t*>(bp + r * bstep + kb);
-    }
-    bf16x8_t bh[NSUB], bl[NSUB];
-#pragma unroll
-    for (int u = 0; u < NSUB; ++u) {
-      const int row = wc * 16 * NSUB + u * 16 + fr;
-      bh[u] = __builtin_bit_cast(bf16x8_t, sB[bb + row * 8 + (frun ^ sw(fr))]);
-      bl[u] = __builtin_bit_cast(bf16x8_t, sB[bb + row * 8 + ((4 + frun) ^ sw(fr))]);
-    }
+    for (int hl = 0; hl < 2; ++hl)
+      f[hl] = __builtin_bit_cast(bf16x8_t, sA[slot * AST + ((wr * 8 + i) * 2 + hl) * 64 + lane]);
+  };
+  aload(0, 0, 0, 4);
+  bload(0, 0);
+  aload(1, 1, 0, 4);
+  bload(1, 1);
+  stage_barrier<4 + NSUB>();
+  bread(bf[0], 0);
+  aread(af[0], 0, 0);
+  int s0 = 0, s1 = 1, s2 = 2;  // A slots of steps st, st + 1, st + 2
+  auto step = [&](long st, auto parity) {
+    constexpr int P = decltype(parity)::value;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int row = wr * 128 + i * 16 + fr;
-      const bf16x8_t ah = __builtin_bit_cast(bf16x8_t, sA[ab + row * 8 + (frun ^ sw(fr))]);
-      const bf16x8_t al = __builtin_bit_cast(bf16x8_t, sA[ab + row * 8 + ((4 + frun) ^ sw(fr))]);
+      if (i < 7) {
+        aread(af[(i + 1) & 1], s0, i + 1);
+        if (i < 4) aload(st + 2, s2, i, i + 1);
+      } else {
+        stage_barrier<4>();  // the next step's operands are there, this step's used up
+        bread(bf[P ^ 1], P ^ 1);
+        aread(af[0], s1, 0);
+        bload(st + 2, P);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < NSUB; ++u) acc[i][u] = mfma3(ah, al, bh[u], bl[u], acc[i][u]);
+      for (int u = 0; u < NSUB; ++u) acc[i][u] = mfma_bf16(af[i & 1][0], bf[P][u][1], acc[i][u]);
+#pragma unroll
+      for (int u = 0; u < NSUB; ++u) acc[i][u] = mfma_bf16(af[i & 1][1], bf[P][u][0], acc[i][u]);
+#pragma unroll
+      for (int u = 0; u < NSUB; ++u) acc[i][u] = mfma_bf16(af[i & 1][0], bf[P][u][0], acc[i][u]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // issue order: the B fragments and the first A pair, then per A row tile its
-    // products with the next pair's reads ahead of them
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * NSUB + 2, 0);
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 3 * NSUB, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 3 * NSUB, 0);
-    if (more) {
-      const int na = ((st + 1) & 1) * ARUNS, nbb = ((st + 1) & 1) * BRUNS;
-#pragma unroll
-      for (int r = 0; r < APER; ++r) sA[na + slo + 512 * r] = ra[r];
-#pragma unroll
-      for (int r = 0; r < BPER; ++r) sB[nbb + slo + 512 * r] = rb[r];
-    }
-    __syncthreads();
+    const int sf = s0;
+    s0 = s1;
+    s1 = s2;
+    s2 = sf;
+  };
+  long st = 0;
+  for (; st + 2 <= nsteps; st += 2) {
+    step(st, std::integral_constant<int, 0>{});
+    step(st + 1, std::integral_constant<int, 1>{});
   }
+  if (st < nsteps) step(st, std::integral_constant<int, 0>{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load is left to land in LDS
   // D[m][n]: lane n + 16*(m/4), element m%4
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -855,32 +889,32 @@ __global__ __launch_bounds__(256) void natural_slots_u16(const uint16_t* __restr
   const int nu = threadIdx.x;
   const size_t kd = static_cast<size_t>(blockIdx.x) * 256 + nu;
   const size_t ks = static_cast<size_t>(blockIdx.x) * 256 + split_slot(nu >> 4, nu & 15);
-  Tn[kd / KB * ts + n * KB + kd % KB] = T[ks / KB * ts + n * KB + ks % KB];
+  Tn[kd / KB * ts + tile_at(n, kd % KB)] = T[ks / KB * ts + tile_at(n, ks % KB)];
 }
 
 // ---------------------------------------------------------------- transpose
-// dst (r', k') = src (k', r') for the 32 x 32 tiles of two tiled operands: src element
-// (r, k) at (k / 32) * sts + r * 32 + k % 32, dst element (r', k') at (k' / 32) * dts +
-// r' * 32 + k' % 32 (16-bit words).  One workgroup moves one contiguous 2 KB tile to
-// another.  grid (dst rows / 32, src rows / 32), block 256
+// dst (r', k') = src (k', r') for the 32 x 32 tiles of two operands in tiles of 32 k
+// (tile_at; sts, dts: elements from one tile to the next, 16-bit words).  One workgroup
+// moves one contiguous 2 KB tile to another.  grid (dst rows / 32, src rows / 32), block 256
 __global__ __launch_bounds__(256) void transpose_tiles_u16(const uint16_t* __restrict__ src, long sts,
                                                            uint16_t* __restrict__ dst, long dts) {
   __shared__ uint16_t tile[32][34];
   const size_t kt = blockIdx.x, rt = blockIdx.y;  // src k tile (= dst row tile), src row tile
-  const int t = threadIdx.x, r = t >> 3, c = (t & 7) * 4;
+  // the thread's four words of a tile: row r, k = c .. c + 3
+  const int t = threadIdx.x, r = (t >> 7) * 16 + ((t >> 1) & 15), c = ((t >> 5) & 3) * 8 + (t & 1) * 4;
   const uint16_t* s = src + kt * sts + rt * (32 * KB);
   uint16_t* d = dst + rt * dts + kt * (32 * KB);
-  const uint2 x = *reinterpret_cast<const uint2*>(s + r * KB + c);
+  const uint2 x = *reinterpret_cast<const uint2*>(s + 4 * t);
   tile[r][c] = static_cast<uint16_t>(x.x);
   tile[r][c + 1] = static_cast<uint16_t>(x.x >> 16);
   tile[r][c + 2] = static_cast<uint16_t>(x.y);
   tile[r][c + 3] = static_cast<uint16_t>(x.y >> 16);
   __syncthreads();
-  // dst row r (= src k c0 + r), columns c .. c + 3 (= src rows)
+  // dst row r (= src k r), columns c .. c + 3 (= src rows)
   uint2 y;
   y.x = static_cast<uint32_t>(tile[c][r]) | (static_cast<uint32_t>(tile[c + 1][r]) << 16);
   y.y = static_cast<uint32_t>(tile[c + 2][r]) | (static_cast<uint32_t>(tile[c + 3][r]) << 16);
-  *reinterpret_cast<uint2*>(d + r * KB + c) = y;
+  *reinterpret_cast<uint2*>(d + 4 * t) = y;
 }
 
 // ---------------------------------------------------------------- split sums
@@ -909,28 +943,11 @@ __global__ __launch_bounds__(256) void sum_splits_f32(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------- host
-// Workgroups of the contraction kernel for (wide, ntw) resident at once on the device.
-static long contract_slots(int wide, int ntw) {
-  const void* f;
-  if (wide) {
-    f = ntw == 8    ? reinterpret_cast<const void*>(&contract2_bf16x3<2>)
-        : ntw == 12 ? reinterpret_cast<const void*>(&contract2_bf16x3<3>)
-                    : reinterpret_cast<const void*>(&contract2_bf16x3<4>);
-    return resident_wgs(f, 512, 1);
-  }
-  switch (ntw) {
-    case 1: f = reinterpret_cast<const void*>(&contract_bf16x3<1>); break;
-    case 2: f = reinterpret_cast<const void*>(&contract_bf16x3<2>); break;
-    case 3: f = reinterpret_cast<const void*>(&contract_bf16x3<3>); break;
-    case 4: f = reinterpret_cast<const void*>(&contract_bf16x3<4>); break;
-    case 5: f = reinterpret_cast<const void*>(&contract_bf16x3<5>); break;
-    case 6: f = reinterpret_cast<const void*>(&contract_bf16x3<6>); break;
-    case 7: f = reinterpret_cast<const void*>(&contract_bf16x3<7>); break;
-    case 8: f = reinterpret_cast<const void*>(&contract_bf16x3<8>); break;
-    default: f = reinterpret_cast<const void*>(&contract_bf16x3<9>); break;
-  }
-  return resident_wgs(f, CNT, 1);
-}
+// Workgroups of the contraction kernel for (wide, ntw) that the splits are balanced against:
+// one per CU, two of the narrow strips.  A constant, not what is resident, because every
+// split is one more FP32 partial sum: the splits, and with them the results, stay when a
+// kernel's registers or LDS change.
+static long contract_slots(int wide, int ntw) { return device_cus() * (wide || ntw > 4 ? 1 : 2); }
 
 // Splits of the contraction's k range for a launch of `rows` rows and 16*ntw-wide
 // column tiles (wide: the 256 x 64 NSUB kernel): at least one full round of resident
@@ -1197,10 +1214,10 @@ int bf16x3_run(const double* B, long qs, long rs, const double* tau, int o, int 
     }
     {
       ProfScope ps(s, "pack_tau_bf16", 0.0, 8.0 * oo * vv + 4.0 * (pv * p.po + pvm * p.pm));
-      pack_tau_bf16_kernel<<<dim3(p.nbp, p.NP), 256, 0, s>>>(tau, o, v, +1, Tph, Tpl);
+      pack_tau_bf16_kernel<<<dim3(p.nbp, p.NP / 16), 256, 0, s>>>(tau, o, v, +1, Tph, Tpl);
       if ((rc = check_launch("pack_tau_bf16(+)"))) break;
       if (p.pm > 0) {
-        pack_tau_bf16_kernel<<<dim3(p.nbp, p.NM), 256, 0, s>>>(tau, o, v, -1, Tmh, Tml);
+        pack_tau_bf16_kernel<<<dim3(p.nbp, p.NM / 16), 256, 0, s>>>(tau, o, v, -1, Tmh, Tml);
         if ((rc = check_launch("pack_tau_bf16(-)"))) break;
       }
     }
@@ -1310,10 +1327,10 @@ int bf16x3_run_sym(const double* B, const double* tau, int o, int v, int naux, d
     }
     {
       ProfScope ps(s, "pack_tau_bf16", 0.0, 0.0);
-      pack_tau_bf16_kernel<<<dim3(p.nbp, p.NP), 256, 0, s>>>(tau, o, v, +1, Tph, Tpl);
+      pack_tau_bf16_kernel<<<dim3(p.nbp, p.NP / 16), 256, 0, s>>>(tau, o, v, +1, Tph, Tpl);
       if ((rc = check_launch("pack_tau_bf16(+)"))) break;
       if (p.pm > 0) {
-        pack_tau_bf16_kernel<<<dim3(p.nbp, p.NM), 256, 0, s>>>(tau, o, v, -1, Tmh, Tml);
+        pack_tau_bf16_kernel<<<dim3(p.nbp, p.NM / 16), 256, 0, s>>>(tau, o, v, -1, Tmh, Tml);
         if ((rc = check_launch("pack_tau_bf16(-)"))) break;
       }
       const dim3 gp(static_cast<unsigned>(p.nbp), p.NP), gm(static_cast<unsigned>(p.nbp), p.NM);
