@@ -104,10 +104,15 @@ __global__ __launch_bounds__(256) void relayout_b_f32(const double* __restrict__
 // out[slot][col], slot = pcd*256 + c_in*16 + d_in, col = packed (i,j).
 // sign > 0: i<=j columns, value of tau+ (with the 1/2 on c == d);
 // sign < 0: i<j columns, value of tau-.  Both taken from the pair-symmetric part
-// of tau, formed in FP64 and rounded once to T.  grid (nbp, ncol/16), block 256
+// of tau, formed in FP64 and rounded once to T.  One launch packs both.
+// grid (nbp, max(NP, NM)/16, 2 signs), block 256
 template <class T>
-__device__ __forceinline__ void pack_body(const double* __restrict__ tau, int o, int v, int ncol, int sign,
-                                          T* __restrict__ out) {
+__device__ __forceinline__ void pack_body(const double* __restrict__ tau, int o, int v, int NP, int NM,
+                                          T* __restrict__ Tp, T* __restrict__ Tm) {
+  const int sign = blockIdx.z == 0 ? 1 : -1, ncol = sign > 0 ? NP : NM;
+  const int col0 = blockIdx.y * NG;
+  if (col0 >= ncol) return;  // uniform over the workgroup
+  T* out = sign > 0 ? Tp : Tm;
   __shared__ double sv[256][NG + 1];
   int Cb, Db;
   tri_decode(blockIdx.x, Cb, Db);
@@ -116,49 +121,61 @@ __device__ __forceinline__ void pack_body(const double* __restrict__ tau, int o,
   const bool valid = d < v && (Cb < Db || c_in <= d_in) && (sign > 0 || c != d);
   const int nreal = sign > 0 ? o * (o + 1) / 2 : o * (o - 1) / 2;
   const size_t vv = static_cast<size_t>(v) * v;
-  for (int cc = 0; cc < NG; ++cc) {
-    const int col = blockIdx.y * NG + cc;
-    double val = 0.0;
-    if (valid && col < nreal) {
+  // four columns at a time, loaded unconditionally (a lane without work reads tau's first
+  // elements and drops them), so that the loads of four columns are in flight together
+  const size_t cd = valid ? static_cast<size_t>(c) * v + d : 0, dc = valid ? static_cast<size_t>(d) * v + c : 0;
+  for (int c0 = 0; c0 < NG; c0 += 4) {
+    double x[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int col = col0 + c0 + k < nreal ? col0 + c0 + k : 0;
       int i, j;
       tri_decode(col, i, j);
-      if (sign < 0) j += 1;
+      if (sign < 0 && col0 + c0 + k < nreal) j += 1;
       const double* tij = tau + (static_cast<size_t>(i) * o + j) * vv;
       const double* tji = tau + (static_cast<size_t>(j) * o + i) * vv;
-      const size_t cd = static_cast<size_t>(c) * v + d, dc = static_cast<size_t>(d) * v + c;
-      const double x1 = tij[cd], x2 = tij[dc], x3 = tji[cd], x4 = tji[dc];
-      if (sign > 0) {
-        val = 0.25 * ((x1 + x4) + (x2 + x3));
-        if (c == d) val *= 0.5;
-      } else {
-        val = 0.25 * ((x1 + x4) - (x2 + x3));
-      }
+      x[k][0] = tij[cd];
+      x[k][1] = tij[dc];
+      x[k][2] = tji[cd];
+      x[k][3] = tji[dc];
     }
-    sv[t][cc] = val;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      double val = 0.0;
+      if (valid && col0 + c0 + k < nreal) {
+        if (sign > 0) {
+          val = 0.25 * ((x[k][0] + x[k][3]) + (x[k][1] + x[k][2]));
+          if (c == d) val *= 0.5;
+        } else {
+          val = 0.25 * ((x[k][0] + x[k][3]) - (x[k][1] + x[k][2]));
+        }
+      }
+      sv[t][c0 + k] = val;
+    }
   }
   __syncthreads();
   for (int r = 0; r < 16; ++r) {
     const int slot = r * 16 + (t >> 4), cc = t & 15;
-    out[(static_cast<size_t>(blockIdx.x) * 256 + slot) * ncol + blockIdx.y * NG + cc] = static_cast<T>(sv[slot][cc]);
+    out[(static_cast<size_t>(blockIdx.x) * 256 + slot) * ncol + col0 + cc] = static_cast<T>(sv[slot][cc]);
   }
 }
-__global__ __launch_bounds__(256) void pack_tau_f64(const double* __restrict__ tau, int o, int v, int ncol, int sign,
-                                                    double* __restrict__ out) {
-  pack_body<double>(tau, o, v, ncol, sign, out);
+__global__ __launch_bounds__(256) void pack_tau_f64(const double* __restrict__ tau, int o, int v, int NP, int NM,
+                                                    double* __restrict__ Tp, double* __restrict__ Tm) {
+  pack_body<double>(tau, o, v, NP, NM, Tp, Tm);
 }
-__global__ __launch_bounds__(256) void pack_tau_f32(const double* __restrict__ tau, int o, int v, int ncol, int sign,
-                                                    float* __restrict__ out) {
-  pack_body<float>(tau, o, v, ncol, sign, out);
+__global__ __launch_bounds__(256) void pack_tau_f32(const double* __restrict__ tau, int o, int v, int NP, int NM,
+                                                    float* __restrict__ Tp, float* __restrict__ Tm) {
+  pack_body<float>(tau, o, v, NP, NM, Tp, Tm);
 }
 
 // ---------------------------------------------------------------- 3a. build
-// One workgroup: ab block pair (Ab, Bb) x a part of cd block pair (Cb, Db): 2 NWC
-// consecutive c by 8 d.  2 NWC waves; wave w owns c in {2*(w>>1), +1} and
-// d in {4*(w&1) .. +3} of the part and accumulates (ac|bd) and (ad|bc) as 16x16 (a, b)
-// MFMA tiles.  A stage of LDS holds, for SK = 8 auxiliary functions, Bc for the
-// 2 NWC + 8 c/d rows x (16 a + 16 b) columns.
+// One workgroup: ab block pair (Ab, Bb) x a part of cd block pair (Cb, Db): CW NWC
+// consecutive c by 2 DW d (CW = 2, DW = 4 but for few block pairs).  2 NWC waves; wave w
+// owns c from CW*(w>>1) and d from DW*(w&1) of the part and accumulates (ac|bd) and (ad|bc)
+// as 16x16 (a, b) MFMA tiles.  A stage of LDS holds, for SK = 8 auxiliary functions, Bc for
+// the CW NWC + 2 DW c/d rows x (16 a + 16 b) columns.
 // The launch covers cd block pairs pcd0 .. nbp-1 (rows of the others are not written).
-// grid ((nbp - pcd0)*16/NWC, slab_pairs), block 128*NWC
+// grid ((nbp - pcd0)*parts, slab_pairs), block 128*NWC
 // D: the workgroups of diagonal ab block pairs (Ab == Bb), blockIdx.y counting them
 // from block Ab = diag_y0; otherwise blockIdx.y is the slab's pair and diagonal pairs
 // exit at once.  In a diagonal pair a and b run over the same block, so the (ad|bc)
@@ -176,18 +193,26 @@ __global__ __launch_bounds__(256) void pack_tau_f32(const double* __restrict__ t
 // between memory and LDS, and [c][Q][a] factors, whose 128-byte pieces lay a whole number
 // of L2 channel rounds apart and queued on one channel); 2.18 ms in FP32 at v=150 naux=421
 // (2.29 ms).
-template <class T, bool D>
+constexpr int BNW = 2;  // pairs of waves per build workgroup
+// Workgroups of the large tiles per CU up to which the small ones are taken.  FP64 with the
+// small against the large tiles: v = 24 13 us against 32 us (two launches), v = 48 the ladder
+// 105 against 119 us, v = 64 (3.1 per CU) 208 against 209 us, FP32 128 against 149 us.
+constexpr long BUILD_SMALL = 4;
+template <class T, bool D, int CW, int DW>
 struct BuildFrag {
-  T a_c[2], b_c[D ? 1 : 2], a_d[D ? 1 : 4], b_d[4];
+  T a_c[CW], b_c[D ? 1 : CW], a_d[D ? 1 : DW], b_d[DW];
 };
-template <class T, bool D, int NWC>
-__device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p, int vp, long slab0, long slab_M,
-                                           int want_minus, int diag_y0, long pcd0, T* __restrict__ Wp,
-                                           T* __restrict__ Wm) {
+// workgroups per cd block pair
+constexpr int build_parts(int cw, int dw) { return (16 / (BNW * cw)) * (16 / (2 * dw)); }
+template <class T, int CW, int DW>
+constexpr int build_lds() { return 3 * (BNW * CW + 2 * DW) * 2 * 8 * TB; }  // elements
+template <class T, bool D, int CW, int DW>
+__device__ __forceinline__ void build_body(T* lds, const T* __restrict__ Bc, int naux_p, int vp, long slab_M,
+                                           int want_minus, int Ab, int Bb, long pab_loc, long pcd, int part,
+                                           T* __restrict__ Wp, T* __restrict__ Wm) {
   typedef Mfma<T> MF;
-  constexpr int NT = 128 * NWC;                // threads
-  constexpr int NC = 2 * NWC, NX = NC + 8;     // c rows, all rows
-  constexpr int PARTS = 16 / NWC;              // workgroups per cd block pair
+  constexpr int NWC = BNW, NT = 128 * NWC;     // pairs of waves, threads
+  constexpr int NC = CW * NWC, ND = 2 * DW, NX = NC + ND;  // c rows, d rows, all rows
   constexpr int VEC = 16 / sizeof(T);          // elements per 16-byte load
   constexpr int SK = 8;                        // auxiliary functions per stage
   constexpr int EV = 16 * SK / VEC;            // loads per (row, a or b block) of a stage: one wave's
@@ -196,22 +221,12 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
   constexpr int NS = SK / 4;                   // MFMA steps per stage
   static_assert(NS % 2 == 0 && KC % SK == 0, "operand registers alternate over whole stages");
   static_assert(NV * NT * VEC == LBUF, "whole loads");
-  __shared__ T lds[3 * LBUF];  // [slot][x: NC c then 8 d][a or b][k][16 e]
-  static_assert(3 * LBUF >= 2 * NWC * 4 * 256, "the ring holds half of the transposed tiles");
-  const int part = blockIdx.x % PARTS;
-  const long pcd = pcd0 + blockIdx.x / PARTS;
-  int Cb, Db, Ab, Bb;
+  // lds: [slot][x: NC c then ND d][a or b][k][16 e]
+  static_assert(3 * LBUF == build_lds<T, CW, DW>(), "the ring");
+  static_assert(3 * LBUF >= 2 * NWC * DW * 256, "the ring holds the transposed tiles of one c per wave");
+  int Cb, Db;
   tri_decode(pcd, Cb, Db);
-  long pab_loc;
-  if constexpr (D) {
-    Ab = Bb = diag_y0 + static_cast<int>(blockIdx.y);
-    pab_loc = static_cast<long>(Ab) * (Ab + 3) / 2 - slab0;
-  } else {
-    pab_loc = blockIdx.y;
-    tri_decode(slab0 + pab_loc, Ab, Bb);
-    if (Ab == Bb) return;  // built by the diagonal launch (uniform over the workgroup)
-  }
-  const int c_off = (part >> 1) * NC, d_off = (part & 1) * 8;
+  const int c_off = part / (16 / ND) * NC, d_off = part % (16 / ND) * ND;
   const int c_base = Cb * TB + c_off, d_base = Db * TB + d_off;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
 
@@ -226,26 +241,26 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
     gp[r] = Bc + (static_cast<size_t>(cg) * (vp / TB) + (h ? Bb : Ab)) * naux_p * TB + ke;
   }
   const int wv = __builtin_amdgcn_readfirstlane(w);
-  const int xc0 = (w >> 1) * 2, xd0 = NC + (w & 1) * 4;
+  const int xc0 = (w >> 1) * CW, xd0 = NC + (w & 1) * DW;
   const int m = lane & 15, kq = lane >> 4;
   const int nst = naux_p / SK;
   // In a diagonal cd block pair a part with all c above all d holds only slots whose
   // packed amplitudes are zero: its W entries are written as zeros without the build
   // (uniform over the workgroup).
-  const bool skip = Cb == Db && c_off > d_off + 7;
+  const bool skip = Cb == Db && c_off > d_off + ND - 1;
   const size_t col0 = static_cast<size_t>(pab_loc) * 256;
 
   {
-    constexpr int NA2 = D ? 1 : 2;  // (ad|bc) accumulators are not needed when D
-    typename MF::acc_t acc1[2][4], acc2[NA2][4];
+    constexpr int NA2 = D ? 1 : CW;  // (ad|bc) accumulators are not needed when D
+    typename MF::acc_t acc1[CW][DW], acc2[NA2][DW];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < CW; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc1[i][j] = MF::zero();
+      for (int j = 0; j < DW; ++j) acc1[i][j] = MF::zero();
 #pragma unroll
     for (int i = 0; i < NA2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc2[i][j] = MF::zero();
+      for (int j = 0; j < DW; ++j) acc2[i][j] = MF::zero();
     if (!skip) {
       auto gload = [&](int st, int slot) {
         const size_t at = static_cast<size_t>(st) * (SK * TB);
@@ -253,25 +268,25 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
         for (int r = 0; r < NV; ++r) load_lds16(gp[r] + at, lds + slot * LBUF + (wv * 64 + NT * r) * VEC);
       };
       const int fc = (xc0 * 2 * SK + kq) * TB + m, fd = (xd0 * 2 * SK + kq) * TB + m;
-      BuildFrag<T, D> f[2];
-      auto fread = [&](BuildFrag<T, D>& q, int slot, int s) {  // step s of the stage in `slot`
+      BuildFrag<T, D, CW, DW> f[2];
+      auto fread = [&](BuildFrag<T, D, CW, DW>& q, int slot, int s) {  // step s of the stage in `slot`
         const T* base = lds + slot * LBUF + s * 4 * TB;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < CW; ++i) {
           q.a_c[i] = base[fc + 2 * i * SK * TB];
           if constexpr (!D) q.b_c[i] = base[fc + (2 * i + 1) * SK * TB];
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < DW; ++j) {
           if constexpr (!D) q.a_d[j] = base[fd + 2 * j * SK * TB];
           q.b_d[j] = base[fd + (2 * j + 1) * SK * TB];
         }
       };
-      auto mma = [&](const BuildFrag<T, D>& q) {
+      auto mma = [&](const BuildFrag<T, D, CW, DW>& q) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < CW; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
+          for (int j = 0; j < DW; ++j) {
             acc1[i][j] = MF::mma(q.a_c[i], q.b_d[j], acc1[i][j]);                    // (ac|bd)
             if constexpr (!D) acc2[i][j] = MF::mma(q.a_d[j], q.b_c[i], acc2[i][j]);  // (ad|bc)
           }
@@ -304,16 +319,16 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
     }  // !skip
 
     // epilogue: W+-[slot][ab slot]; element r of a lane is row a_in = drow(r, lane),
-    // column b_in = lane & 15 of the (a, b) tile.  D: each wave's own 4 x 256 elements of
+    // column b_in = lane & 15 of the (a, b) tile.  D: each wave's own DW x 256 elements of
     // the (now idle) ring hold the (ac|bd) tiles of one c, element (a, b) of a tile at
     // a*16 + (b ^ a), read back transposed.
-    T* tw = lds + w * (4 * 256);
+    T* tw = lds + w * (DW * 256);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < CW; ++i) {
       if constexpr (D) {
         if (i) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < DW; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int a_in = MF::drow(r, lane), b_in = lane & 15;
@@ -322,7 +337,7 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
         __syncthreads();
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < DW; ++j) {
         const int c_in = c_off + xc0 + i, d_in = d_off + (xd0 - NC) + j;
         const size_t row = (static_cast<size_t>(pcd) * 256 + c_in * 16 + d_in) * slab_M + col0;
 #pragma unroll
@@ -341,24 +356,66 @@ __device__ __forceinline__ void build_body(const T* __restrict__ Bc, int naux_p,
     }
   }
 }
-constexpr int BNW = 2;  // c pairs per build workgroup
+#define BUILD_ARGS(T) const T* __restrict__ Bc, int naux_p, int vp, long slab0, long slab_M, int want_minus, \
+                      int diag_y0, long pcd0, T* __restrict__ Wp, T* __restrict__ Wm
 #define BUILD_ATTR(w) __launch_bounds__(128 * BNW) __attribute__((amdgpu_waves_per_eu(w, w)))
-__global__ BUILD_ATTR(2) void build_w_f64(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
-    long slab_M, int want_minus, int diag_y0, long pcd0, double* __restrict__ Wp, double* __restrict__ Wm) {
-  build_body<double, false, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+template <class T, bool D>
+__device__ __forceinline__ void build_launch(BUILD_ARGS(T)) {
+  __shared__ T lds[build_lds<T, 2, 4>()];
+  constexpr int PARTS = build_parts(2, 4);
+  int Ab, Bb;
+  long pab_loc;
+  if constexpr (D) {
+    Ab = Bb = diag_y0 + static_cast<int>(blockIdx.y);
+    pab_loc = static_cast<long>(Ab) * (Ab + 3) / 2 - slab0;
+  } else {
+    pab_loc = blockIdx.y;
+    tri_decode(slab0 + pab_loc, Ab, Bb);
+    if (Ab == Bb) return;  // built by the diagonal launch (uniform over the workgroup)
+  }
+  build_body<T, D, 2, 4>(lds, Bc, naux_p, vp, slab_M, want_minus, Ab, Bb, pab_loc, pcd0 + blockIdx.x / PARTS,
+                         blockIdx.x % PARTS, Wp, Wm);
 }
-__global__ BUILD_ATTR(2) void build_w_f64_diag(const double* __restrict__ Bc, int naux_p, int vp, long slab0,
-    long slab_M, int want_minus, int diag_y0, long pcd0, double* __restrict__ Wp, double* __restrict__ Wm) {
-  build_body<double, true, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+__global__ BUILD_ATTR(2) void build_w_f64(BUILD_ARGS(double)) {
+  build_launch<double, false>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
-__global__ BUILD_ATTR(4) void build_w_f32(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
-    long slab_M, int want_minus, int diag_y0, long pcd0, float* __restrict__ Wp, float* __restrict__ Wm) {
-  build_body<float, false, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+__global__ BUILD_ATTR(2) void build_w_f64_diag(BUILD_ARGS(double)) {
+  build_launch<double, true>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
-__global__ BUILD_ATTR(4) void build_w_f32_diag(const float* __restrict__ Bc, int naux_p, int vp, long slab0,
-    long slab_M, int want_minus, int diag_y0, long pcd0, float* __restrict__ Wp, float* __restrict__ Wm) {
-  build_body<float, true, BNW>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+__global__ BUILD_ATTR(4) void build_w_f32(BUILD_ARGS(float)) {
+  build_launch<float, false>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
 }
+__global__ BUILD_ATTR(4) void build_w_f32_diag(BUILD_ARGS(float)) {
+  build_launch<float, true>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+}
+// Few block pairs: diagonal and off-diagonal ab block pairs in one launch, and smaller tiles
+// per wave (FP64 1 c by 2 d, FP32 2 by 2, for whole 16-byte loads), so that the serial
+// chain over the auxiliary functions is as short as the idle CUs allow.
+// grid ((nbp - pcd0)*parts, slab_pairs), block 128*BNW
+template <class T>
+struct SmallTile {
+  static constexpr int CW = sizeof(T) == 8 ? 1 : 2, DW = 2, PARTS = build_parts(CW, DW);
+};
+template <class T>
+__device__ __forceinline__ void build_small(BUILD_ARGS(T)) {
+  typedef SmallTile<T> S;
+  __shared__ T lds[build_lds<T, S::CW, S::DW>()];
+  int Ab, Bb;
+  const long pab_loc = blockIdx.y, pcd = pcd0 + blockIdx.x / S::PARTS;
+  const int part = blockIdx.x % S::PARTS;
+  tri_decode(slab0 + pab_loc, Ab, Bb);
+  if (Ab == Bb)
+    build_body<T, true, S::CW, S::DW>(lds, Bc, naux_p, vp, slab_M, want_minus, Ab, Bb, pab_loc, pcd, part, Wp, Wm);
+  else
+    build_body<T, false, S::CW, S::DW>(lds, Bc, naux_p, vp, slab_M, want_minus, Ab, Bb, pab_loc, pcd, part, Wp, Wm);
+}
+__global__ __launch_bounds__(128 * BNW) void build_w_f64_small(BUILD_ARGS(double)) {
+  build_small<double>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+}
+__global__ __launch_bounds__(128 * BNW) void build_w_f32_small(BUILD_ARGS(float)) {
+  build_small<float>(Bc, naux_p, vp, slab0, slab_M, want_minus, diag_y0, pcd0, Wp, Wm);
+}
+#undef BUILD_ARGS
 #undef BUILD_ATTR
 
 // ---------------------------------------------------------------- 3b. contract
@@ -367,10 +424,23 @@ __global__ BUILD_ATTR(4) void build_w_f32_diag(const float* __restrict__ Bc, int
 // them) and all columns.  Every row tile streams the whole packed tau, so taller tiles
 // read it fewer times.  The k range may be split over grid.z: split z sums k in
 // [z*kz, min(K, (z+1)*kz)) into C + z*zs, and the unpack adds the splits in order.
+// One launch may hold two products of one shape, the second's splits from za on.
 // grid (ncol/(16*NTW), M/CRM, splits), block 256
+template <class T>
+struct ContractSide {
+  const T *W, *Tt;
+  T* C;
+  long kz;
+};
 template <class T, int NTW>
-__device__ __forceinline__ void contract_body(const T* __restrict__ W, const T* __restrict__ Tt, long K, long M,
-                                              int ncol, T* __restrict__ C, long kz, long zs) {
+__device__ __forceinline__ void contract_body(const ContractSide<T>& sa, const ContractSide<T>& sb, int za, long K,
+                                              long M, int ncol, long zs) {
+  const bool second = static_cast<int>(blockIdx.z) >= za;
+  const int bz = second ? blockIdx.z - za : blockIdx.z;
+  const T* __restrict__ W = second ? sb.W : sa.W;
+  const T* __restrict__ Tt = second ? sb.Tt : sa.Tt;
+  T* __restrict__ C = second ? sb.C : sa.C;
+  const long kz = second ? sb.kz : sa.kz;
   // W rows have stride M (the slab width); C has NTW*16*gridDim.x columns
   typedef Mfma<T> MF;
   typedef typename MF::vec_t vec_t;
@@ -386,11 +456,11 @@ __device__ __forceinline__ void contract_body(const T* __restrict__ W, const T* 
   const long n0 = static_cast<long>(tx) * BN, m0 = static_cast<long>(ty) * CRM;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   {  // this split's k range (every split holds at least one chunk)
-    const long k_lo = blockIdx.z * kz;
+    const long k_lo = bz * kz;
     K = (K < k_lo + kz ? K : k_lo + kz) - k_lo;
     W += k_lo * M + m0;
     Tt += k_lo * ncol + n0;
-    C += blockIdx.z * zs;
+    C += bz * zs;
   }
 
   // staging offsets within a chunk (the chunk loop advances the base pointers)
@@ -474,16 +544,14 @@ __device__ __forceinline__ void contract_body(const T* __restrict__ W, const T* 
       }
 }
 template <int NTW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract_f64(const double* __restrict__ W, const double* __restrict__ Tt,
-                                                    long K, long M, int ncol, double* __restrict__ C, long kz,
-                                                    long zs) {
-  contract_body<double, NTW>(W, Tt, K, M, ncol, C, kz, zs);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract_f64(
+    ContractSide<double> sa, ContractSide<double> sb, int za, long K, long M, int ncol, long zs) {
+  contract_body<double, NTW>(sa, sb, za, K, M, ncol, zs);
 }
 template <int NTW>
-__global__ __launch_bounds__(256) void contract_f32(const float* __restrict__ W, const float* __restrict__ Tt,
-                                                    long K, long M, int ncol, float* __restrict__ C, long kz,
-                                                    long zs) {
-  contract_body<float, NTW>(W, Tt, K, M, ncol, C, kz, zs);
+__global__ __launch_bounds__(256) void contract_f32(ContractSide<float> sa, ContractSide<float> sb, int za, long K,
+                                                    long M, int ncol, long zs) {
+  contract_body<float, NTW>(sa, sb, za, K, M, ncol, zs);
 }
 
 // ---------------------------------------------------------------- 3b'. row contraction
@@ -613,27 +681,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 // A may come as zp (zm) partial sums over k, zs (zsm) elements apart, added here in
 // order.  perm: the rows of a block pair are in the split path's slot order.
 // The kernel is bound by memory latency unless many loads are in flight: a thread sums
-// its 16 rows of one column together (16 loads per split), and reads the R entries of
-// four columns before it writes them back.
-// grid (slab_pairs, ceil(po/16)), block 256
-template <class T>
-__global__ __launch_bounds__(256) void unpack_kernel(const T* __restrict__ S, const T* __restrict__ A,
+// its NC rows of one column together, ZU splits at a time (32 loads for sixteen columns per
+// workgroup), and reads the R entries of four columns before it writes them back.  Where
+// sixteen columns per workgroup leave CUs idle, a workgroup takes four, so that the chains of
+// splits and of columns are shorter: o = 4, v = 24 with twelve splits 12.6 us (22 us with
+// sixteen columns).
+// grid (slab_pairs, ceil(po/NC)), block 256
+template <class T, int NC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void unpack_kernel(const T* __restrict__ S, const T* __restrict__ A,
                                                      int NP, int NM, int o, int v, long slab0,
                                                      double* __restrict__ R, int zp, long zsp, int zm, long zsm,
                                                      int perm) {
-  __shared__ double sS[256][NG + 1];
-  __shared__ double sA[256][NG + 1];
+  constexpr int ZU = NC == 16 ? 2 : 8;  // within the registers of two workgroups per CU
+  constexpr int RS = 256 / NC;          // rows between a thread's rows
+  __shared__ double sS[256][NC + 1];
+  __shared__ double sA[256][NC + 1];
   int Ab, Bb;
   tri_decode(slab0 + blockIdx.x, Ab, Bb);
   const int t = threadIdx.x;
   const int po = o * (o + 1) / 2;
-  const int lam0 = blockIdx.y * NG;
+  const int lam0 = blockIdx.y * NC;
   const size_t row0 = static_cast<size_t>(blockIdx.x) * 256;
   {
-    // column lam = lam0 + cc of rows r * 16 + rr (slot order), r = 0..15
+    // column lam = lam0 + cc of rows r * RS + rr (slot order), r = 0 .. NC - 1
     // Loads are unconditional (a lane without work reads a valid neighbouring column
     // and drops the value), so that they issue back to back.
-    const int cc = t & 15, rr = t >> 4, lam = lam0 + cc;
+    const int cc = t % NC, rr = t / NC, lam = lam0 + cc;
     const bool lv = lam < po;
     const int lamc = lv ? lam : po - 1;
     int i, j;
@@ -643,32 +716,42 @@ __global__ __launch_bounds__(256) void unpack_kernel(const T* __restrict__ S, co
     // pair-symmetric
     const bool anti = lv && i < j;
     const int ja = i < j ? j * (j - 1) / 2 + i : (j > 0 ? j * (j - 1) / 2 + j - 1 : 0);
-    auto srow = [&](int r) { return static_cast<size_t>(perm ? split_slot(r, rr) : r * 16 + rr); };
-    double s[16], x[16];
+    int srow[NC];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = x[r] = 0.0;
-    for (int z = 0; z < zp; ++z) {
-      const T* Sz = S + z * zsp;
-      T u[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) u[r] = Sz[(row0 + srow(r)) * NP + lamc];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] += static_cast<double>(u[r]);
+    for (int r = 0; r < NC; ++r) {
+      const int n = r * RS + rr;
+      srow[r] = perm ? split_slot(n >> 4, n & 15) : n;
     }
-    for (int z = 0; NM > 0 && z < zm; ++z) {
-      const T* Az = A + z * zsm;
-      T u[16];
+    // ZU splits at a time, added in order
+    auto sum = [&](const T* P, int nz, long zs, int ncol, int col, double(*dst)[NC + 1], auto use) {
+      double acc[NC];
+      unsigned at[NC];  // bytes from the block's first row
 #pragma unroll
-      for (int r = 0; r < 16; ++r) u[r] = Az[(row0 + srow(r)) * NM + ja];
+      for (int r = 0; r < NC; ++r) {
+        acc[r] = 0.0;
+        at[r] = (static_cast<unsigned>(srow[r]) * ncol + col) * static_cast<unsigned>(sizeof(T));
+      }
+      for (int z = 0; z < nz; z += ZU) {
+        T u[ZU][NC];
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        x[r] += anti && !(Ab == Bb && r == rr) ? static_cast<double>(u[r]) : 0.0;
-    }
+        for (int k = 0; k < ZU; ++k) {
+          const char* Pz = reinterpret_cast<const char*>(P + static_cast<long>(z + k) * zs + row0 * ncol);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      sS[r * 16 + rr][cc] = s[r];
-      sA[r * 16 + rr][cc] = x[r];
-    }
+          for (int r = 0; r < NC; ++r) u[k][r] = *reinterpret_cast<const T*>(Pz + at[r]);
+          if (z + k + 1 >= nz) break;
+        }
+#pragma unroll
+        for (int k = 0; k < ZU; ++k) {
+#pragma unroll
+          for (int r = 0; r < NC; ++r) acc[r] += use(r) ? static_cast<double>(u[k][r]) : 0.0;
+          if (z + k + 1 >= nz) break;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < NC; ++r) dst[r * RS + rr][cc] = acc[r];
+    };
+    sum(S, zp, zsp, NP, lamc, sS, [](int) { return true; });
+    sum(A, NM > 0 ? zm : 0, zsm, NM, ja, sA, [&](int r) { return anti && !(Ab == Bb && (r * RS + rr) >> 4 == ((r * RS + rr) & 15)); });
   }
   __syncthreads();
   const size_t vv = static_cast<size_t>(v) * v;
@@ -680,7 +763,7 @@ __global__ __launch_bounds__(256) void unpack_kernel(const T* __restrict__ S, co
   const bool ok2 = a2 < v && b2 < v && (Ab < Bb || lo < hi);
   const size_t e1 = static_cast<size_t>(a1) * v + b1, e2 = static_cast<size_t>(b2) * v + a2;
   const int s1 = hi * 16 + lo, s2 = lo * 16 + hi;
-  for (int c0 = 0; c0 < NG; c0 += 4) {
+  for (int c0 = 0; c0 < NC; c0 += 4) {
     double *Rij[4], *Rji[4];
     bool val[4], off[4];
     double q11[4], q12[4], q21[4], q22[4];
@@ -720,10 +803,19 @@ __global__ __launch_bounds__(256) void unpack_kernel(const T* __restrict__ S, co
   }
 }
 
+template <class T>
+static void launch_unpack(const T* S, const T* A, int NP, int NM, int o, int v, long slab0, long npairs, double* R,
+                          int zp, long zsp, int zm, long zsm, hipStream_t s, int perm) {
+  const long po = static_cast<long>(o) * (o + 1) / 2;
+  if (npairs * ((po + 15) / 16) < device_cus())
+    unpack_kernel<T, 4><<<dim3(npairs, (po + 3) / 4), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R, zp, zsp, zm, zsm, perm);
+  else
+    unpack_kernel<T, 16><<<dim3(npairs, (po + 15) / 16), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R, zp, zsp, zm, zsm,
+                                                                    perm);
+}
 void launch_unpack_f32(const float* S, const float* A, int NP, int NM, int o, int v, long slab0, long npairs,
                        double* R, int zp, long zsp, int zm, long zsm, hipStream_t s, int perm) {
-  unpack_kernel<float><<<dim3(npairs, (o * (o + 1) / 2 + NG - 1) / NG), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R,
-                                                                                  zp, zsp, zm, zsm, perm);
+  launch_unpack<float>(S, A, NP, NM, o, v, slab0, npairs, R, zp, zsp, zm, zsm, s, perm);
 }
 
 // ---------------------------------------------------------------- tau
@@ -755,7 +847,7 @@ struct Plan {
 
 // Workgroups of the FP64 contraction kernel for ntw resident at once.
 static const void* contract_fn(int ntw) {
-  typedef void (*F)(const double*, const double*, long, long, int, double*, long, long);
+  typedef void (*F)(ContractSide<double>, ContractSide<double>, int, long, long, int, long);
   static constexpr F f[10] = {contract_f64<1>, contract_f64<2>, contract_f64<3>, contract_f64<4>, contract_f64<5>,
                               contract_f64<6>, contract_f64<7>, contract_f64<8>, contract_f64<9>, contract_f64<10>};
   return reinterpret_cast<const void*>(f[ntw - 1]);
@@ -896,8 +988,8 @@ struct K64 {
                          T* Bc) {
     relayout_b_f64<<<g, 256, 0, s>>>(B, qs, rs, v, naux, vp, np, Bc);
   }
-  static void pack_k(dim3 g, hipStream_t s, const double* tau, int o, int v, int ncol, int sign, T* out) {
-    pack_tau_f64<<<g, 256, 0, s>>>(tau, o, v, ncol, sign, out);
+  static void pack_k(dim3 g, hipStream_t s, const double* tau, int o, int v, int NP, int NM, T* Tp, T* Tm) {
+    pack_tau_f64<<<g, 256, 0, s>>>(tau, o, v, NP, NM, Tp, Tm);
   }
   static void build_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
                       T* Wp, T* Wm) {
@@ -907,10 +999,14 @@ struct K64 {
                            long pcd0, T* Wp, T* Wm) {
     build_w_f64_diag<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
   }
+  static void build_small_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
+                            T* Wp, T* Wm) {
+    build_w_f64_small<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
+  }
   template <int NTW>
-  static void contract_k(dim3 g, hipStream_t s, const T* W, const T* Tt, long K, long M, int ncol, T* C, long kz,
-                         long zs) {
-    contract_f64<NTW><<<g, 256, 0, s>>>(W, Tt, K, M, ncol, C, kz, zs);
+  static void contract_k(dim3 g, hipStream_t s, const ContractSide<T>& a, const ContractSide<T>& b, int za, long K,
+                         long M, int ncol, long zs) {
+    contract_f64<NTW><<<g, 256, 0, s>>>(a, b, za, K, M, ncol, zs);
   }
 };
 struct K32 {
@@ -930,8 +1026,8 @@ struct K32 {
                          T* Bc) {
     relayout_b_f32<<<g, 256, 0, s>>>(B, qs, rs, v, naux, vp, np, Bc);
   }
-  static void pack_k(dim3 g, hipStream_t s, const double* tau, int o, int v, int ncol, int sign, T* out) {
-    pack_tau_f32<<<g, 256, 0, s>>>(tau, o, v, ncol, sign, out);
+  static void pack_k(dim3 g, hipStream_t s, const double* tau, int o, int v, int NP, int NM, T* Tp, T* Tm) {
+    pack_tau_f32<<<g, 256, 0, s>>>(tau, o, v, NP, NM, Tp, Tm);
   }
   static void build_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
                       T* Wp, T* Wm) {
@@ -941,32 +1037,53 @@ struct K32 {
                            long pcd0, T* Wp, T* Wm) {
     build_w_f32_diag<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, y0, pcd0, Wp, Wm);
   }
+  static void build_small_k(dim3 g, hipStream_t s, const T* Bc, int np, int vp, long slab0, long sM, int wm, long pcd0,
+                            T* Wp, T* Wm) {
+    build_w_f32_small<<<g, 128 * BNW, 0, s>>>(Bc, np, vp, slab0, sM, wm, 0, pcd0, Wp, Wm);
+  }
   template <int NTW>
-  static void contract_k(dim3 g, hipStream_t s, const T* W, const T* Tt, long K, long M, int ncol, T* C, long kz,
-                         long zs) {
-    contract_f32<NTW><<<g, 256, 0, s>>>(W, Tt, K, M, ncol, C, kz, zs);
+  static void contract_k(dim3 g, hipStream_t s, const ContractSide<T>& a, const ContractSide<T>& b, int za, long K,
+                         long M, int ncol, long zs) {
+    contract_f32<NTW><<<g, 256, 0, s>>>(a, b, za, K, M, ncol, zs);
   }
 };
 
 // rows: number of C rows (multiple of CRM) computed; ldw: row stride of W.  The k
-// range is split `splits` ways (kz each) into partial outputs rows*ncol apart.
+// range is split za (zb) ways into partial outputs rows*ncol apart.  zb > 0: both products.
 template <class KS>
-static void launch_contract(int ntw, const typename KS::T* W, const typename KS::T* Tt, long K, long ldw, long rows,
-                            int ncol, typename KS::T* C, int splits, long kz, hipStream_t s) {
-  const unsigned gy = static_cast<unsigned>(rows / CRM), gz = static_cast<unsigned>(splits);
+static void launch_contract(int ntw, const ContractSide<typename KS::T>& a, const ContractSide<typename KS::T>& b,
+                            int za, int zb, long K, long ldw, long rows, int ncol, hipStream_t s) {
+  const dim3 g(ncol / (16 * ntw), static_cast<unsigned>(rows / CRM), static_cast<unsigned>(za + zb));
   const long zs = rows * ncol;
   switch (ntw) {
-    case 1: KS::template contract_k<1>(dim3(ncol / 16, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 2: KS::template contract_k<2>(dim3(ncol / 32, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 3: KS::template contract_k<3>(dim3(ncol / 48, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 4: KS::template contract_k<4>(dim3(ncol / 64, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 5: KS::template contract_k<5>(dim3(ncol / 80, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 6: KS::template contract_k<6>(dim3(ncol / 96, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 7: KS::template contract_k<7>(dim3(ncol / 112, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 8: KS::template contract_k<8>(dim3(ncol / 128, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    case 9: KS::template contract_k<9>(dim3(ncol / 144, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
-    default: KS::template contract_k<10>(dim3(ncol / 160, gy, gz), s, W, Tt, K, ldw, ncol, C, kz, zs); break;
+    case 1: KS::template contract_k<1>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 2: KS::template contract_k<2>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 3: KS::template contract_k<3>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 4: KS::template contract_k<4>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 5: KS::template contract_k<5>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 6: KS::template contract_k<6>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 7: KS::template contract_k<7>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 8: KS::template contract_k<8>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    case 9: KS::template contract_k<9>(g, s, a, b, za, K, ldw, ncol, zs); break;
+    default: KS::template contract_k<10>(g, s, a, b, za, K, ldw, ncol, zs); break;
   }
+}
+// Both products of a slab: in one launch where they have the same shape and are few
+// workgroups (each alone leaves CUs idle), else one after the other.
+template <class KS>
+static int contract_both(const Plan& p, const ContractSide<typename KS::T>& a, const ContractSide<typename KS::T>& b,
+                         int zp, int zm, long K, long rows, hipStream_t s) {
+  if (p.pm > 0 && p.ntw_p == p.ntw_m && p.NP == p.NM && p.NP / (16 * p.ntw_p) * (rows / CRM) * zp < device_cus()) {
+    launch_contract<KS>(p.ntw_p, a, b, zp, zm, K, p.slab_M, rows, p.NP, s);
+    return check_launch(KS::contract);
+  }
+  launch_contract<KS>(p.ntw_p, a, a, zp, 0, K, p.slab_M, rows, p.NP, s);
+  RI_TRY(check_launch(KS::contract));
+  if (p.pm > 0) {
+    launch_contract<KS>(p.ntw_m, b, b, zm, 0, K, p.slab_M, rows, p.NM, s);
+    RI_TRY(check_launch(KS::contract));
+  }
+  return RI_OK;
 }
 
 // Steps 1 and 2: factors into their operand layout, tau into T+ and T-.
@@ -983,12 +1100,39 @@ static int stage_inputs(const Plan& p, const double* B_vv, long qs, long rs, con
   }
   {
     ProfScope ps(s, KS::pack, 0.0, 8.0 * oo * vv + es * (pv * p.po + pvm * p.pm));
-    KS::pack_k(dim3(p.nbp, p.NP / NG), s, tau, p.o, p.v, p.NP, +1, Tp);
+    const int NM = p.pm > 0 ? p.NM : 0;
+    KS::pack_k(dim3(p.nbp, std::max(p.NP, NM) / NG, NM > 0 ? 2 : 1), s, tau, p.o, p.v, p.NP, NM, Tp, Tm);
     RI_TRY(check_launch(KS::pack));
-    if (p.pm > 0) {
-      KS::pack_k(dim3(p.nbp, p.NM / NG), s, tau, p.o, p.v, p.NM, -1, Tm);
-      RI_TRY(check_launch(KS::pack));
-    }
+  }
+  return RI_OK;
+}
+
+// Step 3a: W+- of the slab's ab block pairs for cd block pairs pcd0 on; le, ld: element
+// counts of all and of the diagonal pairs, per: FLOP per element.
+template <class KS>
+static int launch_build(const Plan& p, const typename KS::T* Bc, long slab0, long npairs, long pcd0, double le,
+                        double ld, double per, typename KS::T* Wp, typename KS::T* Wm, hipStream_t s) {
+  typedef SmallTile<typename KS::T> Small;
+  constexpr int PARTS = build_parts(2, 4);
+  const int wm = p.pm > 0 ? 1 : 0;
+  const long ncd = p.nbp - pcd0;
+  if (ncd * PARTS * npairs <= BUILD_SMALL * device_cus()) {
+    ProfScope ps(s, KS::build, per * le);
+    KS::build_small_k(dim3(ncd * Small::PARTS, npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, wm, pcd0, Wp, Wm);
+    return check_launch(KS::build);
+  }
+  {
+    // off-diagonal and diagonal ab block pairs in two launches
+    ProfScope ps(s, KS::build, per * (le - ld));
+    KS::build_k(dim3(ncd * PARTS, npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, wm, pcd0, Wp, Wm);
+    RI_TRY(check_launch(KS::build));
+  }
+  int dy0, ndiag;
+  diag_pairs(slab0, npairs, dy0, ndiag);
+  if (ndiag > 0) {
+    ProfScope ps(s, KS::build_diag, per * ld);
+    KS::build_diag_k(dim3(ncd * PARTS, ndiag), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, wm, dy0, pcd0, Wp, Wm);
+    RI_TRY(check_launch(KS::build_diag));
   }
   return RI_OK;
 }
@@ -1015,37 +1159,18 @@ static int run_plan(const Plan& p, const double* B_vv, long qs, long rs, const d
     const long M = npairs * 256;
     double le, lt, ld;
     count_pairs(p.v, slab0, npairs, le, lt, ld);
-    int dy0, ndiag;
-    diag_pairs(slab0, npairs, dy0, ndiag);
     long kzp = 0, kzm = 0;
     const int zp = contract_splits(p.NP, p.ntw_p, M, p.K, p.esize, p.fixed, kzp);
     const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, p.K, p.esize, p.fixed, kzm) : 1;
-    {
-      // per valid (a <= b): the v x v matrix (ac|bd) over all c, d, naux products each;
-      // off-diagonal and diagonal ab block pairs in two launches
-      ProfScope ps(s, KS::build, 2.0 * p.naux * vv * (le - ld));
-      KS::build_k(dim3(p.nbp * (16 / BNW), npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, 0, Wp, Wm);
-      RI_TRY(check_launch(KS::build));
-    }
-    if (ndiag > 0) {
-      ProfScope ps(s, KS::build_diag, 2.0 * p.naux * vv * ld);
-      KS::build_diag_k(dim3(p.nbp * (16 / BNW), ndiag), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, dy0, 0,
-                       Wp, Wm);
-      RI_TRY(check_launch(KS::build_diag));
-    }
+    // per valid (a <= b): the v x v matrix (ac|bd) over all c, d, naux products each
+    RI_TRY(launch_build<KS>(p, Bc, slab0, npairs, 0, le, ld, 2.0 * p.naux * vv, Wp, Wm, s));
     {
       ProfScope ps(s, KS::contract, 2.0 * (le * pv * p.po + lt * pvm * p.pm));
-      launch_contract<KS>(p.ntw_p, Wp, Tp, p.K, p.slab_M, M, p.NP, S, zp, kzp, s);
-      RI_TRY(check_launch(KS::contract));
-      if (p.pm > 0) {
-        launch_contract<KS>(p.ntw_m, Wm, Tm, p.K, p.slab_M, M, p.NM, A, zm, kzm, s);
-        RI_TRY(check_launch(KS::contract));
-      }
+      RI_TRY(contract_both<KS>(p, {Wp, Tp, S, kzp}, {Wm, Tm, A, kzm}, zp, zm, p.K, M, s));
     }
     {
       ProfScope ps(s, KS::unpack, 0.0, 16.0 * oo * (le + lt));
-      unpack_kernel<T><<<dim3(npairs, (p.po + NG - 1) / NG), 256, 0, s>>>(S, A, p.NP, p.NM, p.o, p.v, slab0, R, zp,
-                                                                        M * p.NP, zm, M * p.NM, 0);
+      launch_unpack<T>(S, A, p.NP, p.NM, p.o, p.v, slab0, npairs, R, zp, M * p.NP, zm, M * p.NM, s, 0);
       RI_TRY(check_launch(KS::unpack));
     }
   }
@@ -1138,40 +1263,20 @@ static int run_sym(const Plan& p, const double* B_vv, const double* tau, double*
     double le, lt, ld, ce, ct, cd;
     count_pairs(p.v, slab0, npairs, le, lt, ld);
     count_pairs(p.v, slab0, p.nbp - slab0, ce, ct, cd);
-    int dy0, ndiag;
-    diag_pairs(slab0, npairs, dy0, ndiag);
-    const unsigned gx = static_cast<unsigned>((p.nbp - slab0) * (16 / BNW));
     const double per_ab = 2.0 * p.naux * (2.0 * ct + (ce - ct));
-    {
-      ProfScope ps(s, KS::build, per_ab * (le - ld));
-      KS::build_k(dim3(gx, npairs), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, slab0, Wp, Wm);
-      RI_TRY(check_launch(KS::build));
-    }
-    if (ndiag > 0) {
-      ProfScope ps(s, KS::build_diag, per_ab * ld);
-      KS::build_diag_k(dim3(gx, ndiag), s, Bc, p.naux_p, p.vp, slab0, p.slab_M, p.pm > 0 ? 1 : 0, dy0, slab0, Wp,
-                       Wm);
-      RI_TRY(check_launch(KS::build_diag));
-    }
+    RI_TRY(launch_build<KS>(p, Bc, slab0, npairs, slab0, le, ld, per_ab, Wp, Wm, s));
     const size_t w0 = static_cast<size_t>(slab0) * 256 * p.slab_M;  // row slab0*256 of W
     long kzp = 0, kzm = 0;
     const int zp = contract_splits(p.NP, p.ntw_p, M, K1, p.esize, p.fixed, kzp);
     const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, K1, p.esize, p.fixed, kzm) : 1;
     {
       ProfScope ps(s, KS::contract, 2.0 * (le * ce * p.po + lt * ct * p.pm));
-      launch_contract<KS>(p.ntw_p, Wp + w0, Tp + static_cast<size_t>(slab0) * 256 * p.NP, K1, p.slab_M, M, p.NP, S,
-                          zp, kzp, s);
-      RI_TRY(check_launch(KS::contract));
-      if (p.pm > 0) {
-        launch_contract<KS>(p.ntw_m, Wm + w0, Tm + static_cast<size_t>(slab0) * 256 * p.NM, K1, p.slab_M, M, p.NM,
-                            A, zm, kzm, s);
-        RI_TRY(check_launch(KS::contract));
-      }
+      const size_t t0 = static_cast<size_t>(slab0) * 256;
+      RI_TRY(contract_both<KS>(p, {Wp + w0, Tp + t0 * p.NP, S, kzp}, {Wm + w0, Tm + t0 * p.NM, A, kzm}, zp, zm, K1, M, s));
     }
     {
       ProfScope ps(s, KS::unpack, 0.0, 16.0 * oo * (le + lt));
-      unpack_kernel<T><<<dim3(npairs, (p.po + NG - 1) / NG), 256, 0, s>>>(S, A, p.NP, p.NM, p.o, p.v, slab0, R, zp,
-                                                                        M * p.NP, zm, M * p.NM, 0);
+      launch_unpack<T>(S, A, p.NP, p.NM, p.o, p.v, slab0, npairs, R, zp, M * p.NP, zm, M * p.NM, s, 0);
       RI_TRY(check_launch(KS::unpack));
     }
     if (p1 < p.nbp) {  // second product: rows cd >= P1 of W against the slab's own T rows
@@ -1197,9 +1302,8 @@ static int run_sym(const Plan& p, const double* B_vv, const double* tau, double*
     double le, lt, ld;
     count_pairs(p.v, first_p1, n2, le, lt, ld);
     ProfScope ps(s, KS::unpack, 0.0, 16.0 * oo * (le + lt));
-    unpack_kernel<T><<<dim3(n2, (p.po + NG - 1) / NG), 256, 0, s>>>(
-        S2 + static_cast<size_t>(first_p1) * 256 * p.NP, A2 + static_cast<size_t>(first_p1) * 256 * p.NM, p.NP,
-        p.NM, p.o, p.v, first_p1, R, 1, 0, 1, 0, 0);
+    launch_unpack<T>(S2 + static_cast<size_t>(first_p1) * 256 * p.NP, A2 + static_cast<size_t>(first_p1) * 256 * p.NM,
+                     p.NP, p.NM, p.o, p.v, first_p1, n2, R, 1, 0, 1, 0, s, 0);
     RI_TRY(check_launch(KS::unpack));
   }
   return RI_OK;
