@@ -39,8 +39,9 @@ int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipSt
 // and writes g.c + items[5z + 4] (items on the device, offsets in doubles, those of A and B
 // even); both products have g's extents and strides, but A2's two row levels are exchanged:
 // its row (m1, m2) is at m2 * am1 + m1 * am2.  Both operands k-contiguous and 16-byte
-// aligned, K3 a multiple of 16 (RI_E_ARG otherwise).
-int run_pairs(const GemmDesc& g, int count, const long* items, hipStream_t s);
+// aligned, K3 a multiple of 16 (RI_E_ARG otherwise), of which the first k_used hold anything
+// (k_used > K - 16).
+int run_pairs(const GemmDesc& g, long k_used, int count, const long* items, hipStream_t s);
 
 }  // namespace gemm
 

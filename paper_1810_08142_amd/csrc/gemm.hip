@@ -606,7 +606,8 @@ __device__ __forceinline__ void load_lds16(const void* src, void* dst) {
 // grid (ceil(N/128), ceil(M/128), batch * splits); splits as in gemm_mid.
 // PAIR: batch entry z computes C = A1 B1 + A2 B2 with the two levels of A2's rows exchanged
 // (row (m1, m2) of A2 at m2 am1 + m1 am2); items: per entry the offsets of A1, B1, A2, B2
-// and C.  The summed index runs over the first product, then the second.
+// and C.  The summed index runs over the first product, then the second; cper is the number
+// of k steps (of 4) that hold anything in each product's last chunk.
 // At M = N = K = 16384 (o=32 v=512) 125 ms, 70 TFLOP/s (139 ms through registers).
 template <int AK, int BK, bool PAIR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma(
@@ -698,8 +699,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (ch + 1 < nchunks) load(buf ^ 1);
     fread(0, buf, 0);
+    // PAIR: the zeros that pad a product's last chunk are skipped by whole steps
+    const int steps = PAIR && (ch + 1 == g.K / KC || ch + 1 == nchunks) ? static_cast<int>(cper) : KC / 4;
 #pragma unroll
     for (int s = 0; s < KC / 4; ++s) {
+      if (PAIR && s >= steps) break;
       if (s + 1 < KC / 4) fread((s + 1) & 1, buf, s + 1);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -758,13 +762,13 @@ static void launch_dma(const GemmArgs& ga, int batch, int a_kfast, int b_kfast, 
   else launch_dma_k<0, 0>(ga, batch, nullptr, splits, cper, part, s);
 }
 
-int run_pairs(const GemmDesc& g, int count, const long* items, hipStream_t s) {
+int run_pairs(const GemmDesc& g, long k_used, int count, const long* items, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || count <= 0) return RI_OK;
-  if (g.K <= 0 || !dma_ok(g, 1, 1, 1) || g.am1 % 2) {
+  if (g.K <= 0 || k_used > g.K || k_used <= g.K - KC || !dma_ok(g, 1, 1, 1) || g.am1 % 2) {
     set_error("gemm pairs: operands must be k-contiguous and aligned, K a multiple of %d", KC);
     return RI_E_ARG;
   }
-  launch_dma_k<1, 1, true>(make_args(g), count, items, 1, 0, nullptr, s);
+  launch_dma_k<1, 1, true>(make_args(g), count, items, 1, (k_used - (g.K - KC) + 3) / 4, nullptr, s);
   return check_launch("gemm_dma");
 }
 

@@ -233,11 +233,16 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
   // Buffers: A [o][v][v][v+o], Bt [o][o][v][v+o], J [o][o][v][o], K [o][v][o][v],
   // Y [batch][3][v][v][v] (the pair sums), tile partials, triplet sums, the GEMMs' offsets,
   // the triplets, the tile triples.
-  // Batch: enough GEMM tiles (128 x 128) for four rounds of the chip's two workgroups per CU
-  // (one triplet at v = 120 is 339 tiles, 0.7 rounds), at most 16 triplets and 2 GiB of Y.
+  // Batch: GEMM tiles (128 x 128) for about four rounds of the chip's two workgroups per CU,
+  // at most 16 triplets and 2 GiB of Y.  Of one to three triplets less than four rounds need,
+  // and up to that, the count whose last round is fullest (v = 120, 339 tiles a triplet: six
+  // triplets are 3.97 rounds, seven 4.63).
   const long tiles = 3 * ((vv + 127) / 128) * ((v + 127) / 128);
-  long nb = std::min({(2048 + tiles - 1) / tiles, 16L, (1L << 28) / (3 * v3), ntrip});
-  nb = std::max(1L, nb);
+  const long most = std::max(1L, std::min({(2048 + tiles - 1) / tiles, 16L, (1L << 28) / (3 * v3), ntrip}));
+  long nb = most;
+  auto rounds = [&](long b) { return (b * tiles + 511) / 512; };
+  for (long b = most - 1; b >= std::max(1L, most - 3); --b)
+    if (rounds(b) * nb < rounds(nb) * b) nb = b;  // fewer rounds per triplet
   const size_t nA = static_cast<size_t>(o) * vv * vo, nBt = static_cast<size_t>(o) * o * v * vo,
                nJ = static_cast<size_t>(o) * o * v * o, nK = static_cast<size_t>(o) * v * o * v;
   auto even = [](size_t x) { return (x + 1) / 2 * 2; };
@@ -349,7 +354,7 @@ int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2,
         const long n_t = std::min(nb, ntrip - t0);
         if (precision == RI_PREC_FP64) {
           ProfScope ps(s, "xye,ze->xyz", 12.0 * n_t * static_cast<double>(v3) * vo);
-          rc = gemm::run_pairs(g, static_cast<int>(3 * n_t), items + 15 * t0, s);
+          rc = gemm::run_pairs(g, v + o, static_cast<int>(3 * n_t), items + 15 * t0, s);
         } else {
           for (long x = 0; x < 3 * n_t && rc == RI_OK; ++x) {
             const long* at = &items_host[15 * t0 + 5 * x];
