@@ -204,7 +204,7 @@ struct Ctx {
   int alloc(int level, int slots) {
     m = slots;
     const long vv = static_cast<long>(v) * v, oo = static_cast<long>(o) * o, nn = static_cast<long>(n) * n;
-    std::vector<std::pair<double**, long>> want = {{&gov, noovv}, {&part, EB + 1024}, {&scal, 64}};
+    std::vector<std::pair<double**, long>> want = {{&gov, noovv}, {&part, std::max(EB + 1024, reduce_partials())}, {&scal, 64}};
     if (level >= 1) {
       want.insert(want.end(), {{&h, nn}, {&Lov, noovv}, {&Bd, static_cast<long>(Q) * nn}, {&F, nn}, {&U, noovv},
                                {&X, noovv}, {&G, noovv}, {&Z, noovv}, {&Yb, noovv}, {&W, oo * oo}, {&Gv, vv},
@@ -592,8 +592,7 @@ int ri_ccsd_iterate(const ri_system* sys, double* t1, double* t2, const ri_ccsd_
     float ms_ppl = 0.f;
     RI_TRY(c.residual(tv1, tv2, c.om, c.om + nov, prec, &ms_ppl));
     ms_ppl_total += ms_ppl;
-    RI_TRY(max_abs(c.om, nt, c.part, c.scal, s));
-    RI_TRY(dot(c.om, c.om, nt, c.part, c.scal + 1, s));
+    RI_TRY(norms(c.om, nt, c.part, c.scal, s));
     RI_TRY(c.read_scalars(hostv, 2));
     rinf = hostv[0];
     rrms = std::sqrt(hostv[1] / static_cast<double>(nt));
@@ -636,10 +635,9 @@ int ri_ccsd_iterate(const ri_system* sys, double* t1, double* t2, const ri_ccsd_
         }
       order.push_back(slot);
       const int mm = static_cast<int>(order.size());
-      for (int k = 0; k < mm; ++k) {
-        const double* ek = c.hist + 2L * order[k] * nt + nt;
-        RI_TRY(dot(err, ek, nt, c.part, c.scal + k, s));
-      }
+      const double* ek[MAX_DOTS];  // diis_size is at most 16
+      for (int k = 0; k < mm; ++k) ek[k] = c.hist + 2L * order[k] * nt + nt;
+      RI_TRY(dots(err, ek, mm, nt, c.part, c.scal, s));
       RI_TRY(c.read_scalars(hostv, mm));
       for (int k = 0; k < mm - 1; ++k) gram[k].push_back(hostv[k]);
       gram.push_back(std::vector<double>(hostv, hostv + mm));
@@ -682,7 +680,7 @@ int ri_ccsd_iterate(const ri_system* sys, double* t1, double* t2, const ri_ccsd_
       float ms = 0.f;
       c.other_prec = RI_PREC_FP64;
       RI_TRY(c.residual(tv1, tv2, c.om, c.om + nov, RI_PREC_FP64, &ms));
-      RI_TRY(max_abs(c.om, nt, c.part, c.scal, s));
+      RI_TRY(norms(c.om, nt, c.part, c.scal, s));
       RI_TRY(c.read_scalars(hostv, 1));
       rinf64 = hostv[0];
     }

@@ -83,10 +83,12 @@ int einsum(const char* spec, double alpha, const Tensor& A, const Tensor& B, dou
 // out = alpha * permute(in) + beta * out, with spec like "kiac->aikc" (in -> out letters).
 int axpby_perm(const char* spec, double alpha, const Tensor& in, double beta, const Tensor& out, hipStream_t s);
 
-// Deterministic reductions (fixed blocking and tree order); the result stays on
-// the device at *res.  `part` needs reduce_partials() doubles.
+// Deterministic reductions (fixed blocking and tree order); the results stay on the device.
+// `part` needs reduce_partials() doubles.  dots: res[k] = x . y[k] for k < m <= MAX_DOTS;
+// norms: res[0] = max |x|, res[1] = x . x.
+constexpr int MAX_DOTS = 16;
 int reduce_partials();
-int dot(const double* x, const double* y, long n, double* part, double* res, hipStream_t s);
-int max_abs(const double* x, long n, double* part, double* res, hipStream_t s);
+int dots(const double* x, const double* const* y, int m, long n, double* part, double* res, hipStream_t s);
+int norms(const double* x, long n, double* part, double* res, hipStream_t s);
 
 }  // namespace ri

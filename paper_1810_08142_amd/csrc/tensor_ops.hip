@@ -236,65 +236,119 @@ int axpby_perm(const char* spec, double alpha, const Tensor& in, double beta, co
 }
 
 // ------------------------------------------------------------------ reductions
+// Sums over vectors of the solver.  A short vector takes one launch of one workgroup per
+// result; a long one is read once for all results by RB workgroups, whose partials a second
+// launch adds.  Blocking and tree order depend on the length alone.  Bound by launches
+// (seven results of one iteration at o = 4, v = 24: one launch, 6 us, for fourteen, 36 us)
+// or by the reading (err once and not once per result).
 namespace {
-constexpr int RB = 1024;  // partial sums (fixed, so the reduction order never changes)
+constexpr int RB = 1024;             // partials per result of a long vector
+constexpr long SHORT = 1 << 15;      // elements up to which a vector is short
+struct Vecs {
+  const double* y[MAX_DOTS];
+  int m;
+};
 
-template <int MODE>  // 0: sum x*y, 1: max |x|
-__global__ __launch_bounds__(256) void reduce_stage1(const double* __restrict__ x, const double* __restrict__ y,
-                                                     long n, double* part) {
-  __shared__ double sh[256];
-  const long chunk = (n + RB - 1) / RB;
-  const long lo = static_cast<long>(blockIdx.x) * chunk, hi = std::min(n, lo + chunk);
-  double acc = 0.0;
-  for (long i = lo + threadIdx.x; i < hi; i += 256) {
-    if (MODE == 0) acc += x[i] * y[i];
-    else acc = fmax(acc, fabs(x[i]));
+// sum (MAX: largest) of the 64 lanes, then of the waves in order, valid in thread 0
+template <bool MAX>
+__device__ inline double block_reduce(double x, double* sh) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) {
+    const double z = __shfl_xor(x, w);
+    x = MAX ? fmax(x, z) : x + z;
   }
-  sh[threadIdx.x] = acc;
+  __syncthreads();  // sh may still be read from the reduction before
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      if (MODE == 0) sh[threadIdx.x] += sh[threadIdx.x + w];
-      else sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  x = sh[0];
+  for (int w = 1; w < static_cast<int>(blockDim.x >> 6); ++w) x = MAX ? fmax(x, sh[w]) : x + sh[w];
+  return x;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void reduce_stage2(const double* __restrict__ part, double* res) {
-  __shared__ double sh[256];
+// res[k] = sum_i x[i] y_k[i].  grid m, block 1024
+__global__ __launch_bounds__(1024) void dots_short(const double* __restrict__ x, Vecs v, long n, double* res) {
+  __shared__ double sh[16];
+  const double* __restrict__ y = v.y[blockIdx.x];
   double acc = 0.0;
-  for (int i = threadIdx.x; i < RB; i += 256) {
-    if (MODE == 0) acc += part[i];
-    else acc = fmax(acc, part[i]);
+#pragma unroll 8
+  for (long i = threadIdx.x; i < n; i += 1024) acc += x[i] * y[i];
+  acc = block_reduce<false>(acc, sh);
+  if (threadIdx.x == 0) res[blockIdx.x] = acc;
+}
+// part[k RB + b]: the partials of res[k].  grid RB, block 256
+__global__ __launch_bounds__(256) void dots_stage1(const double* __restrict__ x, Vecs v, long n, double* part) {
+  __shared__ double sh[4];
+  const long chunk = (n + RB - 1) / RB;
+  const long lo = static_cast<long>(blockIdx.x) * chunk, hi = std::min(n, lo + chunk);
+  double acc[MAX_DOTS];
+#pragma unroll
+  for (int k = 0; k < MAX_DOTS; ++k) acc[k] = 0.0;
+  for (long i = lo + threadIdx.x; i < hi; i += 256) {
+    const double xi = x[i];
+#pragma unroll
+    for (int k = 0; k < MAX_DOTS; ++k)
+      if (k < v.m) acc[k] += xi * v.y[k][i];
   }
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      if (MODE == 0) sh[threadIdx.x] += sh[threadIdx.x + w];
-      else sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
+#pragma unroll
+  for (int k = 0; k < MAX_DOTS; ++k)
+    if (k < v.m) {
+      const double z = block_reduce<false>(acc[k], sh);
+      if (threadIdx.x == 0) part[k * RB + blockIdx.x] = z;
     }
-    __syncthreads();
+}
+// res[k] = sum of the partials of k (the first: their maximum if max0).  grid m, block 256
+__global__ __launch_bounds__(256) void dots_stage2(const double* __restrict__ part, int max0, double* res) {
+  __shared__ double sh[4];
+  const bool mx = max0 && blockIdx.x == 0;
+  part += blockIdx.x * RB;
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < RB; i += 256) acc = mx ? fmax(acc, part[i]) : acc + part[i];
+  acc = mx ? block_reduce<true>(acc, sh) : block_reduce<false>(acc, sh);
+  if (threadIdx.x == 0) res[blockIdx.x] = acc;
+}
+// max |x| and sum x^2 of a workgroup's range to out[0] and out[os]
+__global__ __launch_bounds__(1024) void norms_kernel(const double* __restrict__ x, long n, double* out, long os) {
+  __shared__ double sh[16];
+  const long chunk = (n + gridDim.x - 1) / gridDim.x;
+  const long lo = static_cast<long>(blockIdx.x) * chunk, hi = std::min(n, lo + chunk);
+  double mx = 0.0, sq = 0.0;
+#pragma unroll 8
+  for (long i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+    mx = fmax(mx, fabs(x[i]));
+    sq += x[i] * x[i];
   }
-  if (threadIdx.x == 0) *res = sh[0];
+  mx = block_reduce<true>(mx, sh);
+  sq = block_reduce<false>(sq, sh);
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = mx;
+    out[os + blockIdx.x] = sq;
+  }
 }
 }  // namespace
 
-int reduce_partials() { return RB; }
+int reduce_partials() { return MAX_DOTS * RB; }
 
-int dot(const double* x, const double* y, long n, double* part, double* res, hipStream_t s) {
-  reduce_stage1<0><<<RB, 256, 0, s>>>(x, y, n, part);
-  reduce_stage2<0><<<1, 256, 0, s>>>(part, res);
-  return check_launch("dot");
+int dots(const double* x, const double* const* y, int m, long n, double* part, double* res, hipStream_t s) {
+  Vecs v{};
+  v.m = m;
+  for (int k = 0; k < m; ++k) v.y[k] = y[k];
+  if (n <= SHORT) {
+    dots_short<<<m, 1024, 0, s>>>(x, v, n, res);
+  } else {
+    dots_stage1<<<RB, 256, 0, s>>>(x, v, n, part);
+    dots_stage2<<<m, 256, 0, s>>>(part, 0, res);
+  }
+  return check_launch("dots");
 }
 
-int max_abs(const double* x, long n, double* part, double* res, hipStream_t s) {
-  reduce_stage1<1><<<RB, 256, 0, s>>>(x, x, n, part);
-  reduce_stage2<1><<<1, 256, 0, s>>>(part, res);
-  return check_launch("max_abs");
+int norms(const double* x, long n, double* part, double* res, hipStream_t s) {
+  if (n <= SHORT) {
+    norms_kernel<<<1, 1024, 0, s>>>(x, n, res, 1);
+  } else {
+    norms_kernel<<<RB, 256, 0, s>>>(x, n, part, RB);
+    dots_stage2<<<2, 256, 0, s>>>(part, 1, res);
+  }
+  return check_launch("norms");
 }
 
 }  // namespace ri
