@@ -61,11 +61,6 @@ __device__ inline void split_f64(double x, uint16_t& hi, uint16_t& lo) {
   hi = bf16_bits(static_cast<float>(x));
   lo = bf16_bits(static_cast<float>(x - static_cast<double>(bf16_val(hi))));
 }
-__device__ inline void split_f32(float x, uint16_t& hi, uint16_t& lo) {
-  hi = bf16_bits(x);
-  lo = bf16_bits(x - bf16_val(hi));
-}
-
 // the split of two values, packed in a word each (the conversion instruction rounds to
 // nearest even too)
 __device__ inline uint32_t bf16_pair(float x, float y) {
@@ -80,19 +75,12 @@ __device__ inline void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) 
 __device__ inline f32x4_t mfma_bf16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// c += a*b with both split: hi*lo + lo*hi first, then hi*hi
-__device__ inline f32x4_t mfma3(bf16x8_t ah, bf16x8_t al, bf16x8_t bh, bf16x8_t bl, f32x4_t c) {
-  c = mfma_bf16(ah, bl, c);
-  c = mfma_bf16(al, bh, c);
-  return mfma_bf16(ah, bh, c);
-}
 
-// LDS swizzles.  A ds_read_b128 is conflict-free when every group of 8 lanes
-// (32 banks) -- or of 16 lanes (64 banks) -- covers distinct 16-byte bank groups.
-// Build: a row e of 4 runs; run r of row e is stored at r ^ sw4(e).  Contraction:
-// a row of 8 runs (hi/lo x 4); run q of row m is stored at q ^ sw8(m).
+// LDS swizzle of the build's factor rows.  A ds_read_b128 is conflict-free when every group
+// of 8 lanes (32 banks) -- or of 16 lanes (64 banks) -- covers distinct 16-byte bank groups:
+// of a row e of 4 runs, run r is stored at r ^ sw4(e).  Three products per split pair: hi*lo
+// and lo*hi first, then hi*hi.
 __host__ __device__ inline int sw4(int e) { return ((e >> 1) ^ (e >> 2)) & 3; }
-__host__ __device__ inline int sw8(int m) { return (m ^ (m >> 3)) & 7; }
 
 // slot (0..255) of a cd block pair -> (c_in, d_in)
 __host__ __device__ inline void slot_cd(int slot, int& c_in, int& d_in) {
@@ -182,140 +170,131 @@ __global__ __launch_bounds__(256) void pack_tau_bf16_kernel(const double* __rest
 // ---------------------------------------------------------------- build
 // Diagonal ab block pairs (a and b in one block).  One workgroup = the block pair x one
 // half of a cd block pair: the 8 c of half h of block Cb by all 16 d of block Db.  Eight
-// waves; wave w owns c in 8h + 4(w>>2) + 0..3 and d in 4(w&3) + 0..3.  A Q step stages
-// 24 factor rows (8 c, 16 d).  LDS: a ring of three 48 KB slots.  A step occupies two
-// slots (factor rows 0-11 in the first, 12-23 in the second); while step s is computed,
-// the first half of step s + 1 is written into the third slot, and its second half
-// into step s's first slot once every wave has read it.  Each slot holds 16-byte runs
-// [x 12][hl 2][e 32][run 4], the run index XOR-swizzled with sw4(e) so that the lanes of
-// one ds_read_b128 hit distinct banks.  In a diagonal pair the (ad|bc) tile is the
-// transpose of the (ac|bd) tile: only the latter is built, and the epilogue reads it
-// back through LDS.  blockIdx.y counts the diagonal pairs from block Ab = diag_y0; the
-// launch covers cd block pairs pcd0 .. nbp-1.
+// waves; wave w owns c in 8h + 4(w>>2) + 0..3 and d in 4(w&3) + 0..3.  a and b run over
+// the same 16 columns, so a Q step is 24 factor rows (8 c, 16 d) of 16 columns, 48 KB, and
+// the (ad|bc) tile is the transpose of the (ac|bd) tile: only the latter is built, and the
+// epilogue reads it back through LDS.  Steps go straight to a ring of three LDS slots, two
+// steps ahead; runs [x 24][hl 2][e 16][run 4], the run index XOR-swizzled with sw4(e) so
+// that the lanes of one ds_read_b128 hit distinct banks.  One barrier per step, before the
+// last d pair's products, under which the next step's c fragments and first d pair are read.
+// blockIdx.y counts the diagonal pairs from block Ab = diag_y0; the launch covers cd block
+// pairs pcd0 .. nbp-1.  v = 256, Naux = 768 0.68 ms, v = 512, Naux = 1536 8.3 ms (0.97
+// and 13.1 ms with both column blocks staged through registers, two barriers per step).
 // grid ((nbp - pcd0)*2, diagonal pairs), block 512
-constexpr int SLOT = 12 * 2 * 32 * 4;  // runs per LDS slot (48 KB)
+constexpr int DSLOT = 24 * 2 * 16 * 4;  // runs per LDS slot (48 KB)
 __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh, const uint16_t* __restrict__ Bl,
                                                   int Qp, int vp, long slab0, long wts, int want_minus, int diag_y0,
                                                   long pcd0, uint16_t* __restrict__ Wph, uint16_t* __restrict__ Wpl,
                                                   uint16_t* __restrict__ Wmh, uint16_t* __restrict__ Wml) {
-  __shared__ u32x4_t lds[3 * SLOT];
-  static_assert(3 * SLOT * 4 >= 8 * 16 * 256, "the ring holds the transposed tiles");
+  __shared__ u32x4_t lds[3 * DSLOT];
+  static_assert(3 * DSLOT * 4 >= 8 * 16 * 256, "the ring holds the transposed tiles");
   const int half = blockIdx.x & 1;
   const long pcd = pcd0 + (blockIdx.x >> 1);
-  int Cb, Db, Ab, Bb;
+  int Cb, Db;
   tri_decode(pcd, Cb, Db);
-  Ab = Bb = diag_y0 + static_cast<int>(blockIdx.y);
+  const int Ab = diag_y0 + static_cast<int>(blockIdx.y);
   const long pab_loc = static_cast<long>(Ab) * (Ab + 3) / 2 - slab0;
   const int c_base = Cb * TB + half * 8;
   const int d_base = Db * TB;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
 
-  // staging: run r (0..11) of a thread is run id = t + 512*r of the step, i.e. factor
-  // row x = 2r + (t >> 8) (x < 8: c rows, else d rows) with the thread's own
-  // (hl, e, run); runs 0-5 go to the step's first slot, 6-11 to its second.  The hi/lo
-  // array and the row parity are uniform over a wave, so the loads are buffer loads
-  // from two wave-uniform resources with one per-lane byte offset and a uniform offset
-  // per run and Q step.
+  // staging: a wave loads one of the split arrays of every fourth row, 1 KB each, lane
+  // (e, run) from run (run ^ sw4(e)) of column e, to LDS in the order of the lanes
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int hl_w = (wave >> 1) & 1, xt = wave >> 2, e_t = (t >> 2) & 31, run_t = t & 3;
-  const int ag = e_t < 16 ? Ab * TB + e_t : Bb * TB + (e_t - 16);
+  const int hl_w = wave & 1, xq = wave >> 1;
   const uint16_t* src = hl_w ? Bl : Bh;
   const size_t xs = static_cast<size_t>(vp) * Qp;  // elements from one factor row x to the next
   const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(src + static_cast<size_t>(c_base + xt) * xs), 0, -1, 0x00020000);
+      const_cast<uint16_t*>(src + static_cast<size_t>(c_base + xq) * xs), 0, -1, 0x00020000);
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(src + static_cast<size_t>(d_base + xt) * xs), 0, -1, 0x00020000);
-  const int voff = (ag * 32 + run_t * 8) * 2;  // bytes within the Q tile
-  const int xsb2 = static_cast<int>(xs * 4);  // bytes for two factor rows
-  // LDS run of staging run r within its slot: x' = x mod 12 = 2(r mod 6) + xt
-  const int l0 = xt * 256 + (hl_w * 32 + e_t) * 4 + (run_t ^ sw4(e_t));  // + 512 per run
-  auto gload = [&](u32x4_t* dst, int h2, int step) {  // runs 6*h2 .. 6*h2 + 5
-    const int qb = step * vp * QC * 2;  // bytes: one Q tile of vp columns per step
+      const_cast<uint16_t*>(src + static_cast<size_t>(d_base + xq) * xs), 0, -1, 0x00020000);
+  const int voff = ((Ab * TB + (lane >> 2)) * 32 + ((lane & 3) ^ sw4(lane >> 2)) * 8) * 2;
+  const int xsb4 = static_cast<int>(xs * 8);  // bytes for four factor rows
+  u32x4_t* const lw = lds + (xq * 2 + hl_w) * 64;
+  const int nsteps = Qp / QC;
+  auto load = [&](int step, int slot, int k0, int k1) {  // rows xq + 4 k0 .. of the 24
+    const int off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const int r = 6 * h2 + k;
-      dst[k] = __builtin_bit_cast(u32x4_t, r < 4 ? __builtin_amdgcn_raw_buffer_load_b128(rc, voff, r * xsb2 + qb, 0)
-                                                 : __builtin_amdgcn_raw_buffer_load_b128(rd, voff, (r - 4) * xsb2 + qb, 0));
-    }
+    for (int k = k0; k < k1; ++k)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k < 2 ? rc : rd,
+                                               (__attribute__((address_space(3))) void*)(lw + slot * DSLOT + k * 512), 16,
+                                               voff, off + (k < 2 ? k : k - 2) * xsb4, 0, 0);
   };
-  auto lstore = [&](const u32x4_t* sv, int slot) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) lds[slot * SLOT + l0 + 512 * k] = sv[k];
-  };
-  // fragment addresses (run indices) for this lane
-  const int fe = lane & 15, frun = lane >> 4;
-  const int fsw = frun ^ sw4(fe);  // same swizzle for e and e + 16 (sw4 reads bits 1..3)
-  const int xc0 = (w >> 2) * 4, xd0 = 8 + (w & 3) * 4;
+  const int fe = lane & 15, fsw = (lane >> 4) ^ sw4(fe);
+  const u32x4_t* const lc = lds + (w >> 2) * 4 * 128 + fe * 4 + fsw;
+  const u32x4_t* const ld = lds + (8 + (w & 3) * 4) * 128 + fe * 4 + fsw;
 
   f32x4_t o1[4][4], o2[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      o1[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      o2[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int j = 0; j < 4; ++j) o1[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int nsteps = Qp / QC;
   // in a diagonal cd block pair the slots with c > d carry zero amplitudes: a wave whose
-  // 4 x 4 pairs all have c > d skips its products (uniform over the wave)
+  // 4 x 4 pairs all have c > d stores zeros (uniform over the wave)
   const bool zero_w = Cb == Db && half == 1 && (w & 3) < 2;
   {
-    // one Q step from the slots (s0: rows 0-11, s1: rows 12-23) into the accumulators
-    auto compute = [&](int s0, int s1) {
-      auto frag = [&](int x, int hl, int e_off) -> bf16x8_t {
-        const int base = x < 12 ? s0 * SLOT : s1 * SLOT;
-        const int xx = x < 12 ? x : x - 12;
-        const u32x4_t v = lds[base + ((xx * 2 + hl) * 32 + e_off + fe) * 4 + fsw];
-        return __builtin_bit_cast(bf16x8_t, v);
-      };
-      {  // (ac|bd): c fragments of the a rows with d fragments of the b rows
-        bf16x8_t ac[4][2];
+    bf16x8_t cf[2][4][2], df[2][2];
+    auto read_c = [&](bf16x8_t(&f)[4][2], int slot) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int hl = 0; hl < 2; ++hl) ac[i][hl] = frag(xc0 + i, hl, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const bf16x8_t bdh = frag(xd0 + j, 0, 16), bdl = frag(xd0 + j, 1, 16);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) o1[i][j] = mfma3(ac[i][0], ac[i][1], bdh, bdl, o1[i][j]);
-        }
-      }
+        for (int hl = 0; hl < 2; ++hl) f[i][hl] = __builtin_bit_cast(bf16x8_t, lc[slot * DSLOT + (i * 2 + hl) * 64]);
     };
-    u32x4_t sa[6], sb[6];  // first and second half of the next step
-    gload(sa, 0, 0);
-    gload(sb, 1, 0);
-    lstore(sa, 0);
-    lstore(sb, 1);
-    if (nsteps > 1) {
-      gload(sa, 0, 1);
-      gload(sb, 1, 1);
-    }
-    __syncthreads();
-    int s0 = 0;  // slot of the current step's first half; its second half is s0 + 1 mod 3
-    for (int st = 0; st < nsteps; ++st) {
-      const int s1 = s0 == 2 ? 0 : s0 + 1, sf = s1 == 2 ? 0 : s1 + 1;
-      const bool more = st + 1 < nsteps;
-      if (more) {
-        lstore(sa, sf);  // first half of step st + 1 into the free slot
-        if (st + 2 < nsteps) gload(sa, 0, st + 2);
+    auto read_d = [&](bf16x8_t(&f)[2], int slot, int j) {
+#pragma unroll
+      for (int hl = 0; hl < 2; ++hl) f[hl] = __builtin_bit_cast(bf16x8_t, ld[slot * DSLOT + (j * 2 + hl) * 64]);
+    };
+    load(0, 0, 0, 6);
+    load(1, 1, 0, 6);
+    stage_barrier<6>();
+    read_c(cf[0], 0);
+    read_d(df[0], 0, 0);
+    int s0 = 0, s1 = 1, s2 = 2;  // slots of steps st, st + 1, st + 2
+    auto step = [&](int st, bf16x8_t(&c0)[4][2], bf16x8_t(&c1)[4][2]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j < 3) {
+          read_d(df[(j + 1) & 1], s0, j + 1);
+          load(st + 2, s2, 2 * j, 2 * j + 2);
+        } else {
+          stage_barrier<6>();  // the next step is there, this step's slot used up
+          read_d(df[0], s1, 0);
+          read_c(c1, s1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o1[i][j] = mfma_bf16(c0[i][0], df[j & 1][1], o1[i][j]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o1[i][j] = mfma_bf16(c0[i][1], df[j & 1][0], o1[i][j]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o1[i][j] = mfma_bf16(c0[i][0], df[j & 1][0], o1[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (!zero_w) compute(s0, s1);
-      __syncthreads();  // every wave has read slot s0
-      if (more) {
-        lstore(sb, s0);  // second half of step st + 1
-        if (st + 2 < nsteps) gload(sb, 1, st + 2);
-        __syncthreads();
-      }
-      s0 = sf;
+      const int sf = s0;
+      s0 = s1;
+      s1 = s2;
+      s2 = sf;
+    };
+    int st = 0;
+    for (; st + 2 <= nsteps; st += 2) {
+      step(st, cf[0], cf[1]);
+      step(st + 1, cf[1], cf[0]);
     }
+    if (st < nsteps) step(st, cf[0], cf[1]);
+    stage_barrier<0>();  // no load is left to land in the ring, every wave is past its reads
+  }
+  if (zero_w) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o1[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
   {
     // (ad|bc)[a][b] = (ac|bd)[b][a]: each wave stores its sixteen (ac|bd) tiles in its
     // own 16 KB of the ring, element (a, b) at a*16 + (b ^ a), and reads them back
-    // transposed (the loop ended with every wave past its last fragment read)
+    // transposed
     float* tw = reinterpret_cast<float*>(lds) + w * (16 * 256);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -347,33 +326,26 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
     const size_t row = static_cast<size_t>(pab_loc) * 256 + a_in * 16 + b_in;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      uint16_t ph[8], pl[8], mh[8], ml[8];
+      u32x4_t ph, pl, mh, ml;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float v1 = o1[2 * hh + i][j][r], v2 = o2[2 * hh + i][j][r];
-          split_f32(v1 + v2, ph[i * 4 + j], pl[i * 4 + j]);
-          split_f32(v1 - v2, mh[i * 4 + j], ml[i * 4 + j]);
-        }
-      u32x4_t h, l;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        h[k] = static_cast<uint32_t>(ph[2 * k]) | (static_cast<uint32_t>(ph[2 * k + 1]) << 16);
-        l[k] = static_cast<uint32_t>(pl[2 * k]) | (static_cast<uint32_t>(pl[2 * k + 1]) << 16);
+      for (int k2 = 0; k2 < 4; ++k2) {
+        const int i = 2 * hh + (k2 >> 1), j = 2 * (k2 & 1);
+        const float v1 = o1[i][j][r], v2 = o2[i][j][r], u1 = o1[i][j + 1][r], u2 = o2[i][j + 1][r];
+        uint32_t hi, lo;
+        split_pair(v1 + v2, u1 + u2, hi, lo);
+        ph[k2] = hi;
+        pl[k2] = lo;
+        split_pair(v1 - v2, u1 - u2, hi, lo);
+        mh[k2] = hi;
+        ml[k2] = lo;
       }
       const size_t k = slot0 + 8 * hh;
       const size_t at = k / KB * wts + tile_at(row, static_cast<int>(k % KB));
-      *reinterpret_cast<u32x4_t*>(Wph + at) = h;
-      *reinterpret_cast<u32x4_t*>(Wpl + at) = l;
+      *reinterpret_cast<u32x4_t*>(Wph + at) = ph;
+      *reinterpret_cast<u32x4_t*>(Wpl + at) = pl;
       if (want_minus) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          h[k] = static_cast<uint32_t>(mh[2 * k]) | (static_cast<uint32_t>(mh[2 * k + 1]) << 16);
-          l[k] = static_cast<uint32_t>(ml[2 * k]) | (static_cast<uint32_t>(ml[2 * k + 1]) << 16);
-        }
-        *reinterpret_cast<u32x4_t*>(Wmh + at) = h;
-        *reinterpret_cast<u32x4_t*>(Wml + at) = l;
+        *reinterpret_cast<u32x4_t*>(Wmh + at) = mh;
+        *reinterpret_cast<u32x4_t*>(Wml + at) = ml;
       }
     }
   }
