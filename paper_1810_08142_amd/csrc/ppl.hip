@@ -872,8 +872,9 @@ static long fixed_slots(int ntw, size_t esize) {
 // workgroups is not a few stragglers.  At least 32 chunks per split, 4
 // for FP64 on a free workspace, where a small ladder would otherwise leave most of
 // the chip idle (at o=4 v=24 the six workgroups of the whole k range take 32 us, split
-// twelve ways 5 us).  kz: summed indices per split.
-static int contract_splits(int ncol, int ntw, long rows, long K, size_t esize, bool fixed, long& kz) {
+// twelve ways 5 us).  held: rows of partial sums there is room for (0: none yet, the plan
+// is being sized).  kz: summed indices per split.
+static int contract_splits(int ncol, int ntw, long rows, long K, size_t esize, bool fixed, long held, long& kz) {
   const long nwg = (ncol / (16 * ntw)) * (rows / CRM);
   fixed = fixed || esize != 8;
   const long slots = fixed ? fixed_slots(ntw, esize) : contract_slots(ntw);
@@ -883,19 +884,30 @@ static int contract_splits(int ncol, int ntw, long rows, long K, size_t esize, b
   const long zmax = std::max(1L, K / ((fixed ? 32 : 4) * KC));
   z = std::max(1L, std::min(z, zmax));
   z = balance_splits(nwg, slots, K, KC, z, zmax);
+  if (held > 0) z = std::min(z, std::max(1L, held / rows));
   kz = (K + z - 1) / z;
   kz = (kz + KC - 1) / KC * KC;
   return static_cast<int>((K + kz - 1) / kz);
 }
 
-// Largest splits x rows over the slab sizes of plan p (the full slab and the last).
+// Largest splits x rows over the slab sizes of plan p (the full slab and the last) when
+// all K slots are summed.
 static long max_split_rows(const Plan& p, int ncol, int ntw) {
   if (ncol == 0) return 0;
   long kz;
   const long last = p.nbp - (p.nbp - 1) / p.slab_bp * p.slab_bp;
   long best = 0;
-  for (long rows : {p.slab_M, last * 256}) best = std::max(best, contract_splits(ncol, ntw, rows, p.K, p.esize, p.fixed, kz) * rows);
+  for (long rows : {p.slab_M, last * 256}) best = std::max(best, contract_splits(ncol, ntw, rows, p.K, p.esize, p.fixed, 0, kz) * rows);
   return best;
+}
+
+// Splits of one side's contraction (minus: A, else S) over K slots for `rows` rows of plan
+// p, within the partial sums that S or A holds: fewer slots than p.K can ask for more
+// splits than p.K does (a split's slots are rounded up to KC, so the count is not monotone
+// in K), and the exchange-symmetric form sums fewer in every slab but the first.
+static int slab_splits(const Plan& p, bool minus, long rows, long K, long& kz) {
+  return contract_splits(minus ? p.NM : p.NP, minus ? p.ntw_m : p.ntw_p, rows, K, p.esize, p.fixed,
+                         minus ? p.zrows_m : p.zrows_p, kz);
 }
 
 // Element counts and total bytes of plan p for its slab width p.slab_bp.
@@ -1160,8 +1172,8 @@ static int run_plan(const Plan& p, const double* B_vv, long qs, long rs, const d
     double le, lt, ld;
     count_pairs(p.v, slab0, npairs, le, lt, ld);
     long kzp = 0, kzm = 0;
-    const int zp = contract_splits(p.NP, p.ntw_p, M, p.K, p.esize, p.fixed, kzp);
-    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, p.K, p.esize, p.fixed, kzm) : 1;
+    const int zp = slab_splits(p, false, M, p.K, kzp);
+    const int zm = p.pm > 0 ? slab_splits(p, true, M, p.K, kzm) : 1;
     // per valid (a <= b): the v x v matrix (ac|bd) over all c, d, naux products each
     RI_TRY(launch_build<KS>(p, Bc, slab0, npairs, 0, le, ld, 2.0 * p.naux * vv, Wp, Wm, s));
     {
@@ -1267,8 +1279,8 @@ static int run_sym(const Plan& p, const double* B_vv, const double* tau, double*
     RI_TRY(launch_build<KS>(p, Bc, slab0, npairs, slab0, le, ld, per_ab, Wp, Wm, s));
     const size_t w0 = static_cast<size_t>(slab0) * 256 * p.slab_M;  // row slab0*256 of W
     long kzp = 0, kzm = 0;
-    const int zp = contract_splits(p.NP, p.ntw_p, M, K1, p.esize, p.fixed, kzp);
-    const int zm = p.pm > 0 ? contract_splits(p.NM, p.ntw_m, M, K1, p.esize, p.fixed, kzm) : 1;
+    const int zp = slab_splits(p, false, M, K1, kzp);
+    const int zm = p.pm > 0 ? slab_splits(p, true, M, K1, kzm) : 1;
     {
       ProfScope ps(s, KS::contract, 2.0 * (le * ce * p.po + lt * ct * p.pm));
       const size_t t0 = static_cast<size_t>(slab0) * 256;
