@@ -926,9 +926,10 @@ static long contract_slots(int wide, int ntw) { return device_cus() * (wide || n
 // workgroups, and enough that one split's slice of the packed amplitudes (hi and lo
 // words, ncol rows of K/z) stays within RI_PPL_TAU_CHUNK_MB (default TAU_CHUNK_MB), for
 // the reason given with the FP64 path's splits; then balanced so that the last round of
-// workgroups is not a few stragglers.  At least 32 steps per split.  kz: summed indices
-// per split.
-static int contract_splits(int wide, int ntw, int ncol, long rows, long K, long& kz) {
+// workgroups is not a few stragglers.  At least 32 steps per split.  held: rows of partial
+// sums there is room for (0: none yet, the plan is being sized).  kz: summed indices per
+// split.
+static int contract_splits(int wide, int ntw, int ncol, long rows, long K, long held, long& kz) {
   const long nwg = (ncol / (16 * ntw)) * (rows / CBM);
   const long slots = contract_slots(wide, ntw);
   long z = (slots + nwg - 1) / nwg;
@@ -937,6 +938,7 @@ static int contract_splits(int wide, int ntw, int ncol, long rows, long K, long&
   const long zmax = std::max(1L, K / (32 * KB));
   z = std::max(1L, std::min(z, zmax));
   z = balance_splits(nwg, slots, K, KB, z, zmax);
+  if (held > 0) z = std::min(z, std::max(1L, held / rows));
   kz = (K + z - 1) / z;
   kz = (kz + KB - 1) / KB * KB;
   return static_cast<int>((K + kz - 1) / kz);
@@ -967,15 +969,24 @@ struct MPlan {
   size_t bytes;
 };
 
-// Largest splits x rows over the slab sizes of plan p (the full slab and the last).
+// Largest splits x rows over the slab sizes of plan p (the full slab and the last) when
+// all K slots are summed.
 static long max_split_rows(const MPlan& p, int wide, int ncol, int ntw) {
   if (ncol == 0) return 0;
   long kz;
   const long last = p.nbp - (p.nbp - 1) / p.slab_bp * p.slab_bp;
   long best = 0;
   for (long rows : {p.slab_M, last * 256})
-    best = std::max(best, contract_splits(wide, ntw, ncol, rows, p.K, kz) * rows);
+    best = std::max(best, contract_splits(wide, ntw, ncol, rows, p.K, 0, kz) * rows);
   return best;
+}
+
+// Splits of one side's contraction (minus: A, else S) over K slots for `rows` rows of plan
+// p, within the partial sums that S or A holds (fewer slots than p.K can ask for more
+// splits, as in the FP64 path).
+static int slab_splits(const MPlan& p, bool minus, long rows, long K, long& kz) {
+  return contract_splits(minus ? p.wide_m : p.wide_p, minus ? p.ntw_m : p.ntw_p, minus ? p.NM : p.NP, rows, K,
+                         minus ? p.zrows_m : p.zrows_p, kz);
 }
 
 // Element counts and total bytes of plan p for its slab width p.slab_bp.
@@ -1202,8 +1213,8 @@ int bf16x3_run(const double* B, long qs, long rs, const double* tau, int o, int 
       int dy0, ndiag;
       diag_pairs(slab0, npairs, dy0, ndiag);
       long kzp = 0, kzm = 0;
-      const int zp = contract_splits(p.wide_p, p.ntw_p, p.NP, M, p.K, kzp);
-      const int zm = p.pm > 0 ? contract_splits(p.wide_m, p.ntw_m, p.NM, M, p.K, kzm) : 1;
+      const int zp = slab_splits(p, false, M, p.K, kzp);
+      const int zm = p.pm > 0 ? slab_splits(p, true, M, p.K, kzm) : 1;
       {  // off-diagonal and diagonal ab block pairs in two launches
         ProfScope ps(s, "build_w_bf16x3", 2.0 * naux * vv * (le - ld));
         launch_build(Bh, Bl, p, slab0, npairs, 0, Wph, Wpl, Wmh, Wml, s);
@@ -1337,8 +1348,8 @@ int bf16x3_run_sym(const double* B, const double* tau, int o, int v, int naux, d
         if ((rc = check_launch("build_w_bf16x3_diag"))) break;
       }
       long kzp = 0, kzm = 0;
-      const int zp = contract_splits(p.wide_p, p.ntw_p, p.NP, M, K1, kzp);
-      const int zm = p.pm > 0 ? contract_splits(p.wide_m, p.ntw_m, p.NM, M, K1, kzm) : 1;
+      const int zp = slab_splits(p, false, M, K1, kzp);
+      const int zm = p.pm > 0 ? slab_splits(p, true, M, K1, kzm) : 1;
       const size_t c0 = static_cast<size_t>(slab0) * 256;  // first cd slot built for the slab
       {
         ProfScope ps(s, "contract_bf16x3", 2.0 * (le * ce * p.po + lt * ct * p.pm));

@@ -38,7 +38,8 @@ def test_fp64_matches_oracle(o, v, naux):
     assert np.array_equal(got, _run(ppl.ppl_sym, B, T))
 
 
-@pytest.mark.parametrize("precision,o,v,naux", [("fp32", 25, 177, 9), ("fp32", 16, 230, 9)])
+@pytest.mark.parametrize("precision,o,v,naux", [("fp32", 25, 177, 9), ("fp32", 16, 230, 9), ("bf16x3", 4, 290, 9),
+                                                 ("bf16x3", 44, 261, 9)])
 def test_reduced_precision_matches_the_plain_ladder(precision, o, v, naux):
     from paper_1810_08142_amd import ppl
     print(f"ppl_sym {precision} o={o} v={v} naux={naux}", flush=True)

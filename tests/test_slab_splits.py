@@ -11,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-@pytest.mark.parametrize("source,flags", [("ppl.hip", [])])
+@pytest.mark.parametrize("source,flags", [("ppl.hip", []), ("ppl_bf16.hip", ["-DSPLIT_BF16"])])
 def test_no_slab_needs_more_partial_sums_than_are_held(source, flags, tmp_path):
     exe = tmp_path / "slab_splits"
     src = os.path.join(ROOT, "paper_1810_08142_amd", "csrc", source)
