@@ -725,19 +725,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void u
     // ZU splits at a time, added in order
     auto sum = [&](const T* P, int nz, long zs, int ncol, int col, double(*dst)[NC + 1], auto use) {
       double acc[NC];
-      unsigned at[NC];  // bytes from the block's first row
+      unsigned at[NC];
 #pragma unroll
       for (int r = 0; r < NC; ++r) {
         acc[r] = 0.0;
-        at[r] = (static_cast<unsigned>(srow[r]) * ncol + col) * static_cast<unsigned>(sizeof(T));
+        at[r] = unpack_at(srow[r], ncol, col);
       }
       for (int z = 0; z < nz; z += ZU) {
         T u[ZU][NC];
 #pragma unroll
         for (int k = 0; k < ZU; ++k) {
-          const char* Pz = reinterpret_cast<const char*>(P + static_cast<long>(z + k) * zs + row0 * ncol);
+          const T* Pz = P + static_cast<long>(z + k) * zs + row0 * ncol;
 #pragma unroll
-          for (int r = 0; r < NC; ++r) u[k][r] = *reinterpret_cast<const T*>(Pz + at[r]);
+          for (int r = 0; r < NC; ++r) u[k][r] = Pz[at[r]];
           if (z + k + 1 >= nz) break;
         }
 #pragma unroll

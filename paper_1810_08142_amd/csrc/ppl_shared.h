@@ -34,6 +34,13 @@ __host__ __device__ inline int split_slot(int x_in, int y_in) {
   return 128 * (x_in >> 3) + 16 * (4 * ((x_in >> 2) & 1) + (y_in >> 2)) + 4 * (x_in & 3) + (y_in & 3);
 }
 
+// Elements from a block pair's first row to element (row, col) of its ncol columns.  The 256
+// rows hold below 2^32 elements for every accepted o (o <= 4096: 8.4e6 columns), which their
+// bytes do not from o = 2050 on.
+__host__ __device__ inline unsigned unpack_at(int row, int ncol, int col) {
+  return static_cast<unsigned>(row) * ncol + col;
+}
+
 // Contraction column tiling: ntw 16-wide column tiles per workgroup tile (1..maxw),
 // chosen to minimise the padded column count (ties: wider tiles).
 // Columns per contraction tile (ntw tiles of 16) for ncols output columns.  A tile
