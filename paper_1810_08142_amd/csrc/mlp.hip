@@ -1210,28 +1210,42 @@ inline ScrSize scr_size(const ri_mlp* net, long rows) {
   z.part = round_up(z.part, 4);
   return z;
 }
+// Scratch for `rows` rows and `deltas` delta buffers, at least what was held.  Where that does
+// not fit the device: what is asked for, or else two delta buffers, with which gradient()
+// goes layer by layer.
 int reserve(ri_mlp* net, long rows, int deltas, hipStream_t s) {
   rows = round_up(rows, 32);  // whole row tiles
   if (rows <= net->rows && deltas <= net->deltas) return RI_OK;
-  rows = std::max(rows, net->rows);
-  deltas = std::max(deltas, net->deltas);
-  const size_t h = net->hidden;
-  const size_t n = static_cast<size_t>(rows);
-  const ScrSize z = scr_size(net, rows);
-  const size_t floats = net->layers * n * h + deltas * n * h + 2 * n + z.part + z.cs + LB + 16;
+  const struct {
+    long rows;
+    int deltas;
+  } tries[] = {{std::max(rows, net->rows), std::max(deltas, net->deltas)}, {rows, deltas}, {rows, 2}};
   if (net->scratch) dev_free(net->scratch, s);
   net->scratch = nullptr;
   net->rows = 0;
   net->deltas = 0;
+  const size_t h = net->hidden;
   void* p = nullptr;
-  RI_TRY(dev_alloc(&p, floats * sizeof(float), s));
-  net->scratch = static_cast<float*>(p);
-  net->rows = rows;
-  net->deltas = deltas;
-  net->scratch_bytes = floats * sizeof(float);
-  return RI_OK;
+  size_t floats = 0;
+  int rc = RI_OK;
+  for (const auto& x : tries) {
+    const size_t n = static_cast<size_t>(x.rows);
+    const ScrSize z = scr_size(net, x.rows);
+    const size_t want = (net->layers + x.deltas) * n * h + 2 * n + z.part + z.cs + LB + 16;
+    if (rc != RI_OK && want == floats) continue;  // the same again
+    floats = want;
+    rc = dev_alloc(&p, floats * sizeof(float), s);
+    if (rc != RI_OK) continue;
+    clear_error();
+    net->scratch = static_cast<float*>(p);
+    net->rows = x.rows;
+    net->deltas = x.deltas;
+    net->scratch_bytes = floats * sizeof(float);
+    break;
+  }
+  return rc;
 }
-// delta buffers that gradient() needs: one per layer where the weight gradients follow all
+// delta buffers that gradient() wants: one per layer where the weight gradients follow all
 // deltas, two in turn where each follows its own
 inline int grad_deltas(const ri_mlp* net) { return step_ok(net) ? std::max(2, net->layers) : 2; }
 
@@ -1334,7 +1348,7 @@ static int step_gradient(ri_mlp* net, const float* X, const float* Y, long n, fl
 
 // grad (device) and loss (device scalar in scratch) for the batch
 int gradient(ri_mlp* net, const float* X, const float* Y, long n, float* grad, hipStream_t s) {
-  if (step_ok(net)) {
+  if (step_ok(net) && net->deltas >= net->layers) {
     switch (net->hidden / 64) {
       case 1: return step_gradient<1>(net, X, Y, n, grad, s);
       case 2: return step_gradient<2>(net, X, Y, n, grad, s);
