@@ -839,8 +839,17 @@ static Choice choose(const GemmDesc& g, int batch) {
   return c;
 }
 
+// Large tiles, whole, when they still give the chip a few workgroups per CU
+// (RI_GEMM_LARGE_MIN_TILES overrides the threshold, e.g. to test the path at small sizes).
+static bool large_tiles(const GemmDesc& g, int batch) {
+  const char* env = getenv("RI_GEMM_LARGE_MIN_TILES");
+  const long env_tiles = env ? strtol(env, nullptr, 10) : 0;
+  const long min_tiles = env_tiles > 0 ? env_tiles : 256;
+  return g.K3 % KC == 0 && ((g.M + BL - 1) / BL) * ((g.N + BL - 1) / BL) * batch >= min_tiles;
+}
+
 size_t scratch_doubles(const GemmDesc& g, int batch) {
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || batch <= 0) return 0;
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || batch <= 0 || large_tiles(g, batch)) return 0;
   const Choice c = choose(g, batch);
   return c.splits > 1 ? static_cast<size_t>(c.splits) * g.M * g.N : 0;
 }
@@ -854,13 +863,7 @@ int run(const GemmDesc& g, int batch, double* scratch, size_t scratch_len, hipSt
   const GemmArgs ga = make_args(g);
   Choice c = choose(g, batch);
   const int a_kfast = c.a_kfast, b_kfast = c.b_kfast;
-  // large tiles when they still give the chip a few workgroups per CU
-  // (RI_GEMM_LARGE_MIN_TILES overrides the threshold, e.g. to test the path at small sizes)
-  const char* env = getenv("RI_GEMM_LARGE_MIN_TILES");
-  const long env_tiles = env ? strtol(env, nullptr, 10) : 0;
-  const long min_tiles = env_tiles > 0 ? env_tiles : 256;
-  const long tiles_l = ((g.M + BL - 1) / BL) * ((g.N + BL - 1) / BL) * batch;
-  if (g.K3 % KC == 0 && tiles_l >= min_tiles) {
+  if (large_tiles(g, batch)) {
     dim3 grid(static_cast<unsigned>((g.N + BL - 1) / BL), static_cast<unsigned>((g.M + BL - 1) / BL),
               static_cast<unsigned>(batch));
     if (prec == RI_PREC_FP32) {
