@@ -683,10 +683,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 // The kernel is bound by memory latency unless many loads are in flight: a thread sums
 // its NC rows of one column together, ZU splits at a time (32 loads for sixteen columns per
 // workgroup), and reads the R entries of four columns before it writes them back.  Where
-// sixteen columns per workgroup leave CUs idle, a workgroup takes four, so that the chains of
-// splits and of columns are shorter: o = 4, v = 24 with twelve splits 12.6 us (22 us with
-// sixteen columns).
-// grid (slab_pairs, ceil(po/NC)), block 256
+// sixteen columns per workgroup leave most CUs idle, a workgroup takes four, so that the
+// chains of splits and of columns are shorter: o = 4, v = 24 with twelve splits 12.6 us (22 us
+// with sixteen columns).  Four columns are a quarter of the lines they lie in: the groups of
+// one block pair run on one XCD, one after the other, so that its L2 serves the other three
+// (FP32 o = 12, v = 80 15 us; 26 us with the pairs fastest and the groups on all XCDs).
+// grid (slab_pairs, ceil(po/NC)), NC = 4 (ceil(po/NC), slab_pairs), block 256
 template <class T, int NC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void unpack_kernel(const T* __restrict__ S, const T* __restrict__ A,
                                                      int NP, int NM, int o, int v, long slab0,
@@ -696,12 +698,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void u
   constexpr int RS = 256 / NC;          // rows between a thread's rows
   __shared__ double sS[256][NC + 1];
   __shared__ double sA[256][NC + 1];
+  unsigned pair = blockIdx.x, group = blockIdx.y;
+  if constexpr (NC == 4) xcd_tile(group, pair);
   int Ab, Bb;
-  tri_decode(slab0 + blockIdx.x, Ab, Bb);
+  tri_decode(slab0 + pair, Ab, Bb);
   const int t = threadIdx.x;
   const int po = o * (o + 1) / 2;
-  const int lam0 = blockIdx.y * NC;
-  const size_t row0 = static_cast<size_t>(blockIdx.x) * 256;
+  const int lam0 = group * NC;
+  const size_t row0 = static_cast<size_t>(pair) * 256;
   {
     // column lam = lam0 + cc of rows r * RS + rr (slot order), r = 0 .. NC - 1
     // Loads are unconditional (a lane without work reads a valid neighbouring column
@@ -803,12 +807,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void u
   }
 }
 
+// Four columns per workgroup while sixteen would give fewer than 3/8 (FP64) or 5/8 (FP32) of
+// the CUs a workgroup.  Four against sixteen columns, FP64: 90 workgroups of sixteen (o = 6,
+// v = 144) 44 against 47 us, 105 (o = 12, v = 96) 89 against 85 us; FP32: 156 (o = 6, v = 192)
+// 46 against 48 us, 165 (o = 8, v = 160) 59 against 56 us, 225 (o = 12, v = 144) 86 against 70
+// us.
 template <class T>
 static void launch_unpack(const T* S, const T* A, int NP, int NM, int o, int v, long slab0, long npairs, double* R,
                           int zp, long zsp, int zm, long zsm, hipStream_t s, int perm) {
   const long po = static_cast<long>(o) * (o + 1) / 2;
-  if (npairs * ((po + 15) / 16) < device_cus())
-    unpack_kernel<T, 4><<<dim3(npairs, (po + 3) / 4), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R, zp, zsp, zm, zsm, perm);
+  if (npairs * ((po + 15) / 16) < device_cus() * (sizeof(T) == 8 ? 3 : 5) / 8)
+    unpack_kernel<T, 4><<<dim3((po + 3) / 4, npairs), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R, zp, zsp, zm, zsm, perm);
   else
     unpack_kernel<T, 16><<<dim3(npairs, (po + 15) / 16), 256, 0, s>>>(S, A, NP, NM, o, v, slab0, R, zp, zsp, zm, zsm,
                                                                     perm);
