@@ -209,11 +209,11 @@ __device__ __forceinline__ void build_diag_body(const uint16_t* __restrict__ Bh,
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(src + static_cast<size_t>(d_base + xq) * xs), 0, -1, 0x00020000);
   const int voff = ((Ab * TB + (lane >> 2)) * 32 + ((lane & 3) ^ sw4(lane >> 2)) * 8) * 2;
-  const int xsb4 = static_cast<int>(xs * 8);  // bytes for four factor rows
+  const unsigned xsb4 = static_cast<unsigned>(xs * 8);  // bytes for four factor rows
   u32x4_t* const lw = lds + (xq * 2 + hl_w) * 64;
   const int nsteps = Qp / QC;
   auto load = [&](int step, int slot, int k0, int k1) {  // rows xq + 4 k0 .. of the 24
-    const int off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
+    const unsigned off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
 #pragma unroll
     for (int k = k0; k < k1; ++k)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(k < 2 ? rc : rd,
@@ -439,13 +439,13 @@ __device__ __forceinline__ void build_split_body(const uint16_t* __restrict__ Bh
   const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(src + static_cast<size_t>(d_base + xt) * xs), 0, -1, 0x00020000);
   const int voff = (((eb_w ? Bb : Ab) * TB + (lane >> 2)) * 32 + ((lane & 3) ^ sw4(lane >> 2)) * 8) * 2;
-  const int xsb2 = static_cast<int>(xs * 4);  // bytes for two factor rows
+  const unsigned xsb2 = static_cast<unsigned>(xs * 4);  // bytes for two factor rows
   u32x4_t* const lw = lds + (xt * 2 + hl_w) * 128 + eb_w * 64;
   const int nsteps = Qp / QC;
   // row pairs k0 .. k1 - 1 of a chunk of a Q step: all c rows, or d rows 0 .. 3 and 8 .. 11,
   // or (x2 = 2) 4 .. 7 and 12 .. 15
   auto load = [&](const __amdgpu_buffer_rsrc_t& rs, int x2, int step, int slot, int k0, int k1) {
-    const int off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
+    const unsigned off = min(step, nsteps - 1) * vp * QC * 2;  // past the end: loaded, not read
 #pragma unroll
     for (int k = k0; k < k1; ++k)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lw + slot * CHK + k * 512),
@@ -1019,8 +1019,8 @@ static bool make_mplan(int o, int v, int naux, MPlan& p, size_t fit_bytes = 0) {
   p.nb = (v + TB - 1) / TB;
   p.vp = p.nb * TB;
   p.Qp = static_cast<int>(round_up(naux, QC));
-  // the build's buffer loads reach eight factor rows of vp * Qp bf16 words past their
-  // base with 32-bit byte offsets
+  // the build's buffer loads reach up to fifteen factor rows of vp * Qp bf16 words past their
+  // base with unsigned 32-bit byte offsets
   if (static_cast<double>(p.vp) * p.Qp * 2 * 8 >= 2147483648.0) return false;
   p.nbp = static_cast<long>(p.nb) * (p.nb + 1) / 2;
   p.K = p.nbp * 256;
