@@ -95,8 +95,10 @@ int ri_ppl_ex(const double* B_vv, const double* tau, int o, int v, int naux, dou
  * RI_PPL_NOALLOC_MAX_BYTES (64 MiB) on every device that loads it, held until the
  * process ends; the call allocates and frees nothing (the per-kernel event profiler
  * stays off for it).  The slab of (ab) block pairs is the widest whose workspace fits
- * that array, so results can differ from ri_ppl_ex in rounding only (the summation
- * order of the contraction's k splits).  Sizes whose one-block-pair plan does not fit
+ * that array, and the FP64 contraction is split over its summed index less finely than
+ * ri_ppl_ex splits it for small ladders, so that the partial sums fit too: results can
+ * differ from ri_ppl_ex in rounding (the summation order of the splits), and small FP64
+ * ladders take longer.  Sizes whose one-block-pair plan does not fit
  * return RI_E_NOMEM and change nothing; as a guide, the FP64 workspace is about
  * 8 vp^2 naux_p + 2 * 8 K (o^2/2 + 256) bytes with vp = v rounded up to 16,
  * naux_p = naux rounded up to 16 and K = 128 (vp/16)(vp/16 + 1), so o = 8, v = 96,
@@ -292,15 +294,18 @@ int ri_ccsd_iterate(const ri_system* sys, double* t1, double* t2, const ri_ccsd_
  * with W, V and D as defined there; written to *e_t (host).  The occupied triplets
  * i <= j <= k are visited once each (W and V of the other orderings are permutations
  * of theirs).  Cost ri_ccsd_triples_flops(o, v) = o(o+1)(o+2) 2 v^3 (v+o) FLOP;
- * device workspace of o v^2 (v+o) + o^2 v (v+o) + o^3 v + o^2 v^2 + 8 v^3 doubles
- * (plus small buffers) is taken stream-ordered.  Synchronises stream; RI_E_NUMERIC if the energy is not
+ * device workspace of o v^2 (v+o) + o^2 v (v+o) + o^3 v + o^2 v^2 + 3 b v^3 doubles (b
+ * triplets are taken together: at most 16, and no more than 2 GiB of the last term unless one
+ * triplet needs it), 140 bytes per triplet and small buffers is taken stream-ordered.  Synchronises stream; RI_E_NUMERIC if the energy is not
  * finite. */
 int ri_ccsd_triples(const ri_system* sys, const double* t1, const double* t2, double* e_t, void* stream);
 /* The same with a choice of arithmetic for the term GEMMs: RI_PREC_FP64, or RI_PREC_FP32
  * (operands rounded to FP32, FP32 MFMA with FP32 accumulation over the summed index of
  * v + o, where the GEMM takes its 128 x 128 tile kernel; W, V and the energy sum stay
- * FP64).  The FP32 error of E_(T) was 1e-8 of its size at o = 24, v = 384.  RI_E_ARG
- * for other precision values. */
+ * FP64).  The FP32 error of E_(T) was 1e-8 of its size at o = 24, v = 384.  The FP64 form
+ * takes the terms in pairs, many to a launch, the FP32 form one by one: at o = 24, v = 384 it
+ * is 4% faster, and up to v = 128, where its GEMMs run in FP64 on smaller tiles, several times
+ * slower than the FP64 form.  RI_E_ARG for other precision values. */
 int ri_ccsd_triples_ex(const ri_system* sys, const double* t1, const double* t2, int precision, double* e_t,
                        void* stream);
 double ri_ccsd_triples_flops(int o, int v);
@@ -336,7 +341,10 @@ int ri_mlp_forward(ri_mlp* net, const float* X, long n, float* y, void* stream);
 int ri_mlp_infer(const ri_mlp* net, const float* X, long n, float* y, void* stream);
 /* Loss and its gradient (device FP32 [num_params]; NULL uses internal storage) on a
  * batch of n <= 2^24 rows; the loss is written to *loss_host when not NULL
- * (synchronises stream).  Deterministic (fixed reduction order). */
+ * (synchronises stream).  Deterministic (fixed reduction order).  Hidden widths 64, 128, 192
+ * and 256 keep one delta of n * hidden floats per layer besides the activations; where the
+ * device does not hold those, two deltas, and the layers are taken one after the other (the
+ * sums over the rows in another order). */
 int ri_mlp_gradient(ri_mlp* net, const float* X, const float* Y, long n, float* grad, float* loss_host,
                     void* stream);
 /* One Adam step with learning rate lr on the batch; *loss_host gets the batch loss

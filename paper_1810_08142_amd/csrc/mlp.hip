@@ -640,7 +640,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // 1.6 GFLOP (11 us of the FP32 matrix pipe), so what counts is the number of dependent
 // launches and that every CU has work in each: layer by layer (one GEMM per product, tanh',
 // and two column-sum stages per layer) it took 21 launches of 2-46 us, 341 us with the loss
-// read back; now step 28, weight gradients 6.4, sums 2.4 us, 70 us in all.
+// read back; now step 29, weight gradients 16, sums 6 us, 70 us in all.
 //
 // step_kernel: forward, loss and backward of 16 RT rows per workgroup, everything between
 // the layers in LDS; H (activations) and D (deltas) also go to memory for the weight
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // RT = 2 halves the weight traffic per row and is taken where every CU still gets a
 // workgroup.  Alone on a CU a workgroup of 16 rows takes 20 us: 7 us of MFMAs, the rest the
 // tanh and the chain load - product - barrier of the layers; two workgroups per CU overlap
-// those (65536 rows: 232 us, MFMAs 109 us).
+// those (65536 rows: 219 us, MFMAs 109 us).
 // Sums over the rows that are no products (biases, output layer, loss) are kept per
 // workgroup in cs [workgroup][CSW]: layers x HID bias sums, HID output weights, the output
 // bias, a gap, the squared error in FP64 (in FP32 the sums over tiles and workgroups, one

@@ -20,7 +20,8 @@
 // z: X(p, q, r; x, y, z) and X(q, p, r; y, x, z), both [x][y][z] with a summed index of their
 // own, so each pair is one GEMM over the two summed indices one after the other (the second
 // A read with its rows (x, y) exchanged).  Per batch: one launch of three such GEMMs per
-// triplet on the library's MFMA engine (FP64 or FP32), each writing its pair's sum in its
+// triplet on the library's MFMA engine (FP64; with FP32 terms two GEMMs per pair, one after
+// the other, the second adding to the first), each writing its pair's sum in its
 // own natural layout (contiguous output rows; the o-sized sum of a term rides along as extra
 // columns of the summed index), and one tiled kernel that symmetrises the three into W,
 // forms V = W + the t1 terms and sums the energy in a fixed order, all in LDS.  The GEMM
